@@ -1028,15 +1028,26 @@ __device__ __forceinline__ float4 mlp_activate(f4 o)
 struct Composite {
     float r = 0.0f, g = 0.0f, b = 0.0f, T = 1.0f;
 
-    __device__ __forceinline__ bool add(float4 s, float delta, float t_term)
+    // (sigma, r, g, b) of a sample to (alpha, r, g, b)
+    static __device__ __forceinline__ float4 opacity(float4 s, float delta)
     {
-        const float alpha = 1.0f - fast_exp(-fmaxf(s.x * delta, 0.0f));
-        const float w = T * alpha;
+        s.x = 1.0f - fast_exp(-fmaxf(s.x * delta, 0.0f));
+        return s;
+    }
+
+    __device__ __forceinline__ bool blend(float4 s, float t_term)
+    {
+        const float w = T * s.x;
         r += w * s.y;
         g += w * s.z;
         b += w * s.w;
-        T *= 1.0f - alpha;
+        T *= 1.0f - s.x;
         return T >= t_term;
+    }
+
+    __device__ __forceinline__ bool add(float4 s, float delta, float t_term)
+    {
+        return blend(opacity(s, delta), t_term);
     }
 
     __device__ __forceinline__ float4 finish(float bgr, float bgg, float bgb) const
