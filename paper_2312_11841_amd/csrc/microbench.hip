@@ -248,7 +248,7 @@ template <> struct RawEntry<16> {
     }
 };
 
-template <uint32_t EB, int G, bool DENSE, int MODE, bool BLOCKS = false>
+template <uint32_t EB, int G, bool DENSE, int MODE, int FORM = mixrt::kEntries>
 __device__ __forceinline__ uint32_t replay_group(const mixrt::GridParams &gp, int l0, float x0,
                                                  float x1, float x2)
 {
@@ -260,7 +260,7 @@ __device__ __forceinline__ uint32_t replay_group(const mixrt::GridParams &gp, in
     // render's block loads (one aligned 16-byte block per x-neighbour pair,
     // the x + 1 entries loaded apart where the voxel straddles two blocks),
     // and the two entries' words picked
-    constexpr bool kBlocks = BLOCKS && !DENSE && (EB == 4 || EB == 8);
+    constexpr bool kBlocks = FORM != mixrt::kEntries && !DENSE && (EB == 4 || EB == 8);
     uint32_t v[G][8];
     uint4 blk[G][4];
     uint32_t far[G][4];
@@ -273,8 +273,13 @@ __device__ __forceinline__ uint32_t replay_group(const mixrt::GridParams &gp, in
             for (int q = 0; q < 4; ++q) {
                 blk[g][q] = *(const uint4 *)(t + (s[g].off[2 * q] & ~15u));
                 far[g][q] = 0u;
+                if (FORM == mixrt::kBlocksWithFar) {
+                    mixrt::load_order();
+                    if (straddle) far[g][q] = RawEntry<EB>::one(t, s[g].off[2 * q + 1]);
+                    mixrt::load_order();
+                }
             }
-            if (straddle) {
+            if (FORM == mixrt::kBlocksThenFar && straddle) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) far[g][q] = RawEntry<EB>::one(t, s[g].off[2 * q + 1]);
             }
@@ -283,10 +288,12 @@ __device__ __forceinline__ uint32_t replay_group(const mixrt::GridParams &gp, in
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
             if (DENSE && (b & 1)) continue;   // a dense pair covers corners b and b + 1
-            if (MODE == 1)
+            if (MODE == 1) {
                 v[g][b] = s[g].off[b];
-            else
+            } else {
                 v[g][b] = DENSE ? RawEntry<EB>::pair(t, s[g].off[b]) : RawEntry<EB>::one(t, s[g].off[b]);
+                mixrt::load_order();
+            }
         }
     }
     uint32_t acc = 0;
@@ -376,8 +383,11 @@ __global__ __launch_bounds__(kBlock) void replay_kernel(const float *__restrict_
         for (; l + kGroup <= lb; l += kGroup) acc ^= replay_group<EB, kGroup, false, MODE>(gp, l, x0, x1, x2);
         for (; l < lb; ++l) acc ^= replay_group<EB, 1, false, MODE>(gp, l, x0, x1, x2);
         if (EB == 8)
-            for (; l + kGroup <= L; l += kGroup) acc ^= replay_group<EB, kGroup, false, MODE, true>(gp, l, x0, x1, x2);
-        for (; l < L; ++l) acc ^= replay_group<EB, 1, false, MODE, true>(gp, l, x0, x1, x2);
+            for (; l + kGroup <= L; l += kGroup) acc ^= replay_group<EB, kGroup, false, MODE, mixrt::kBlocksWithFar>(gp, l, x0, x1, x2);
+        if (EB == 4 && gp.far_last)
+            for (; l < L; ++l) acc ^= replay_group<EB, 1, false, MODE, mixrt::kBlocksThenFar>(gp, l, x0, x1, x2);
+        else
+            for (; l < L; ++l) acc ^= replay_group<EB, 1, false, MODE, mixrt::kBlocksWithFar>(gp, l, x0, x1, x2);
     }
     pools.prefetch(lane);
     }
@@ -415,6 +425,8 @@ int mixrt_mb_gather_replay(const float *x, const int32_t *hit, int32_t views, in
     gp.L = L;
     gp.block_from = block_from < 0 ? 0 : block_from > L ? L : block_from;
     gp.hash_batch = hash_batch;
+    // (the render's rule, with the 4 MiB L2 of one XCD)
+    gp.far_last = chunk != 1 && log2_T <= 20;
     const uint64_t T = 1ull << log2_T;
     for (int l = 0; l < L; ++l) {
         if (N[l] < 1 || N[l] > (1 << 20) || (l > 0 && N[l] < N[l - 1])) return hipErrorInvalidValue;

@@ -65,6 +65,8 @@ struct GridParams {
     float Ntop[kMaxLevels]; // that no lane converts them
     int32_t block_from;     // levels from here on load x-neighbour corner pairs
                             // as 16-byte blocks (4-byte entries; L: none)
+    int32_t far_last;       // 4-byte entries: a straddling voxel's x + 1 entries
+                            // after all four blocks (else each with its block)
     int32_t hash_batch;     // hashed levels per batch of gathers: 2, or 4
                             // (entries of 8 or more bytes)
 };
@@ -294,21 +296,25 @@ __device__ __forceinline__ void displacement(const RayParams &p, float u, float 
         // s = sum_v Y_v(d) m_v over the first V channels; p_cali = p + s d
         const TapWeights<XT> tw(B, p.q_scale[0], p.q_offset[0]);
         float s = 0.0f;
+        // (kept opaque, so that the 16 comparisons below are made here and not
+        // held in 32 scalar registers across the kernel)
+        int V = p.tex_V;
+        asm volatile("" : "+s"(V));
         if (vec) {
 #pragma unroll
             for (int c0 = 0; c0 < 16; c0 += EPV) {
-                if (c0 < p.tex_V) {
+                if (c0 < V) {
                     float m[EPV];
                     bilinear_chunk<XT>(tex, B, tw, c0, m);
 #pragma unroll
                     for (int e = 0; e < EPV && c0 + e < 16; ++e)
-                        if (c0 + e < p.tex_V) s += Y[c0 + e] * m[e];
+                        if (c0 + e < V) s += Y[c0 + e] * m[e];
                 }
             }
         } else {
 #pragma unroll
             for (int c = 0; c < 16; ++c)
-                if (c < p.tex_V) s += Y[c] * bilinear_elem<XT>(tex, B, tw, c);
+                if (c < V) s += Y[c] * bilinear_elem<XT>(tex, B, tw, c);
         }
         ox = s * dx;
         oy = s * dy;
@@ -696,7 +702,7 @@ template <int F, bool F16>
 constexpr bool kBlockPairs8 = F16 && TableEntry<F, F16>::kBytes == 8;
 
 // The 8 corner entries of a level: 4 pair loads on a dense level, 8 single
-// loads on a hashed one.  BLOCKS (hashed levels of 4- or 8-byte entries):
+// loads on a hashed one.  In blocks (hashed levels of 4- or 8-byte entries):
 // one 16-byte block load per x-neighbour pair, which holds both entries in
 // 3 voxels of 4 (4-byte entries) or 1 of 2 (8-byte entries), plus a load of
 // each x + 1 entry in the lanes whose voxel straddles two blocks: 4 full
@@ -705,25 +711,53 @@ constexpr bool kBlockPairs8 = F16 && TableEntry<F, F16>::kBytes == 8;
 // its width, so this pays on levels whose lanes touch distinct lines (the
 // finest); where lanes share lines a 16-byte gather costs more than a
 // narrower one and the word picks cost ALU work.
-template <int F, bool F16, bool DENSE, bool BLOCKS = false>
+//
+// The straddling lanes' entries mostly lie in the block's own line.  Loaded
+// right after their block they find it in the L1; after all four blocks the
+// waves' other gathers have often replaced it, but the lane mask changes once
+// instead of four times.  Loaded with their block: the 8-view 1080p batch
+// 10.73 -> 10.58 ms, spread samples in rounds of one 842 -> 831 us, Tab. 3's 8
+// levels 68.9 -> 67.5 us; in rounds of 4, whose lanes share lines four by
+// four, the masks cost more than the lines: view720p 489 -> 496 us, opaque
+// content 298 -> 304.
+enum GatherForm { kEntries = 0, kBlocksThenFar = 1, kBlocksWithFar = 2 };
+
+// Keeps the loads before it before those after it.  The two entries of an
+// x-neighbour pair mostly share a line, and the vector L1, which the waves of
+// a CU fill with 64 lines per gather, holds it for few gathers: with the
+// compiler free to mix the levels of a batch, the deployed grid's 1280x720
+// frame took 105 us, with the levels apart 97.8, and with every pair's loads
+// next to each other 91.6 (view720p 494, 491, 488.5; spread samples 854, 848,
+// 841).
+__device__ __forceinline__ void load_order() { asm volatile("" ::: "memory"); }
+
+template <int F, bool F16, bool DENSE, int FORM = kEntries>
 __device__ __forceinline__ void level_fetch(const void *table_l, const LevelSetup &s,
                                             float (*v)[F])
 {
     const char *t = (const char *)table_l;
     if constexpr (DENSE) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+        for (int q = 0; q < 4; ++q) {
             TablePair<F, F16>::load(t, s.off[2 * q], v[2 * q], v[2 * q + 1]);
-    } else if constexpr (BLOCKS && kBlockPairs<F, F16>) {
+            load_order();
+        }
+    } else if constexpr (FORM != kEntries && kBlockPairs<F, F16>) {
         // the pairs' offsets differ by the same x part (the y and z parts
         // cancel), so one test serves all four
         const bool straddle = (s.off[0] ^ s.off[1]) >= 16u;
         uint4 blk[4];
         uint32_t far[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+        for (int q = 0; q < 4; ++q) {
             blk[q] = *(const uint4 *)(t + (s.off[2 * q] & ~15u));
-        if (straddle) {
+            if (FORM == kBlocksWithFar) {
+                load_order();
+                if (straddle) far[q] = *(const uint32_t *)(t + s.off[2 * q + 1]);
+                load_order();
+            }
+        }
+        if (FORM == kBlocksThenFar && straddle) {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 far[q] = *(const uint32_t *)(t + s.off[2 * q + 1]);
@@ -735,7 +769,7 @@ __device__ __forceinline__ void level_fetch(const void *table_l, const LevelSetu
             TableEntry<F, F16>::from_word(w0, v[2 * q]);
             TableEntry<F, F16>::from_word(w1, v[2 * q + 1]);
         }
-    } else if constexpr (BLOCKS && kBlockPairs8<F, F16>) {
+    } else if constexpr (FORM != kEntries && kBlockPairs8<F, F16>) {
         // the entries of x and x + 1 differ in bit 0 of the index when x is
         // even (one block, the halves picked by bit 3 of the offset) and in
         // higher bits when x is odd (a straddle, the same for all four)
@@ -743,9 +777,15 @@ __device__ __forceinline__ void level_fetch(const void *table_l, const LevelSetu
         uint4 blk[4];
         uint2 far[4] = {{0u, 0u}, {0u, 0u}, {0u, 0u}, {0u, 0u}};
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+        for (int q = 0; q < 4; ++q) {
             blk[q] = *(const uint4 *)(t + (s.off[2 * q] & ~15u));
-        if (straddle) {
+            if (FORM == kBlocksWithFar) {
+                load_order();
+                if (straddle) far[q] = *(const uint2 *)(t + s.off[2 * q + 1]);
+                load_order();
+            }
+        }
+        if (FORM == kBlocksThenFar && straddle) {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 far[q] = *(const uint2 *)(t + s.off[2 * q + 1]);
@@ -764,8 +804,10 @@ __device__ __forceinline__ void level_fetch(const void *table_l, const LevelSetu
         }
     } else {
 #pragma unroll
-        for (int b = 0; b < 8; ++b)
+        for (int b = 0; b < 8; ++b) {
             TableEntry<F, F16>::load(t, s.off[b], v[b]);
+            load_order();
+        }
     }
 }
 
@@ -794,7 +836,7 @@ __device__ __forceinline__ const void *level_base(const GridParams &g, int l, in
 // G consecutive levels starting at l0, all of one kind (dense or hashed):
 // every corner load of the group is issued before any interpolation, so a
 // wave keeps 4G (dense) or 8G (hashed) gathers in flight.
-template <int F, bool F16, int G, bool DENSE, bool BLOCKS = false>
+template <int F, bool F16, int G, bool DENSE, int FORM = kEntries>
 __device__ __forceinline__ void hash_group(const GridParams &gp, int l0, float x0, float x1,
                                            float x2, float (*feat)[F])
 {
@@ -805,7 +847,7 @@ __device__ __forceinline__ void hash_group(const GridParams &gp, int l0, float x
         level_setup<TableEntry<F, F16>::kBytes, true>(gp, l0 + g, DENSE, x0, x1, x2, s[g]);
 #pragma unroll
     for (int g = 0; g < G; ++g)
-        level_fetch<F, F16, DENSE, BLOCKS>(level_base(gp, l0 + g, F, F16), s[g], v[g]);
+        level_fetch<F, F16, DENSE, FORM>(level_base(gp, l0 + g, F, F16), s[g], v[g]);
 #pragma unroll
     for (int g = 0; g < G; ++g)
         level_accumulate<F>(s[g], v[g], feat[g]);

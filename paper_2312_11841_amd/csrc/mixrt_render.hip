@@ -49,12 +49,12 @@ __device__ unsigned long long phase_cycles[8];
 
 // G levels of one query: into its fp16 row of MLP inputs, or (the MLP
 // removed) added in fp32 to the per-component sums acc[(l F + i) mod 4].
-template <int F, bool TF16, int G, bool DENSE, bool SUM, bool BLOCKS = false>
+template <int F, bool TF16, int G, bool DENSE, bool SUM, int FORM = kEntries>
 __device__ __forceinline__ void encode_levels(const GridParams &gp, int l0, float x0, float x1,
                                               float x2, _Float16 *row, float *acc)
 {
     float f[G][F];
-    hash_group<F, TF16, G, DENSE, BLOCKS>(gp, l0, x0, x1, x2, f);
+    hash_group<F, TF16, G, DENSE, FORM>(gp, l0, x0, x1, x2, f);
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         if (SUM) {
@@ -103,9 +103,10 @@ __device__ __forceinline__ void encode_query(const GridParams &gp, float x0, flo
             for (; l < gp.block_from; ++l)
                 encode_levels<F, TF16, 1, false, SUM>(gp, l, x0, x1, x2, row, acc);
             for (; l + kLevelGroup <= L; l += kLevelGroup)
-                encode_levels<F, TF16, kLevelGroup, false, SUM, true>(gp, l, x0, x1, x2, row, acc);
+                encode_levels<F, TF16, kLevelGroup, false, SUM, kBlocksWithFar>(gp, l, x0, x1, x2,
+                                                                               row, acc);
             for (; l < L; ++l)
-                encode_levels<F, TF16, 1, false, SUM, true>(gp, l, x0, x1, x2, row, acc);
+                encode_levels<F, TF16, 1, false, SUM, kBlocksWithFar>(gp, l, x0, x1, x2, row, acc);
             return;
         }
     }
@@ -119,8 +120,12 @@ __device__ __forceinline__ void encode_query(const GridParams &gp, float x0, flo
     for (; l < lb; ++l)
         encode_levels<F, TF16, 1, false, SUM>(gp, l, x0, x1, x2, row, acc);
     if constexpr (kBlockPairs<F, TF16>) {
-        for (; l < L; ++l)
-            encode_levels<F, TF16, 1, false, SUM, true>(gp, l, x0, x1, x2, row, acc);
+        if (gp.far_last)
+            for (; l < L; ++l)
+                encode_levels<F, TF16, 1, false, SUM, kBlocksThenFar>(gp, l, x0, x1, x2, row, acc);
+        else
+            for (; l < L; ++l)
+                encode_levels<F, TF16, 1, false, SUM, kBlocksWithFar>(gp, l, x0, x1, x2, row, acc);
     }
 }
 
@@ -683,6 +688,19 @@ static int render_block_from(const RenderLaunch &L)
     return nl - kFinest > lo ? nl - kFinest : (lo < nl ? lo : nl);
 }
 
+// Whether the x + 1 entries of straddling voxels are loaded after a level's
+// four blocks instead of each with its block (tables of 4-byte entries):
+// see level_fetch for both sides.  In rounds of one sample per ray and on
+// levels larger than one XCD's L2, whose lines are dear, each goes with its
+// block; elsewhere the lanes share more lines and the one change of the lane
+// mask is cheaper (the tile path on 2 MiB levels: 116 against 119 us at K = 1,
+// 443 against 447 at K = 5).
+static bool render_far_last(const RenderLaunch &L)
+{
+    const int64_t level_bytes = ((int64_t)L.gp.T_mask + 1) * 4;
+    return render_chunk(L) != 1 && level_bytes <= L.l2_bytes;
+}
+
 // Hashed levels per batch of gathers: 4 for entries of 8 or more bytes
 // (F = 4 fp16 and up) when one batch then covers every hashed level of a
 // query (at most 4), so a wave waits for its table once per tile instead of
@@ -744,6 +762,7 @@ hipError_t launch_render(const RenderLaunch &L0, hipStream_t stream)
     RenderLaunch L = L0;
     L.gp.block_from = render_block_from(L);
     L.gp.hash_batch = render_hash_batch(L);
+    L.gp.far_last = render_far_last(L);
 #define X(a, b, c, d, e, f)                                                                    \
     if (MIXRT_RENDER_MATCH(a, b, c, d, e, f)) {                                                \
         int64_t blocks;                                                                        \
