@@ -366,11 +366,11 @@ __global__ __launch_bounds__(kBlock) void replay_kernel(const float *__restrict_
         const int ray = (tp.view * H + j0 + dy) * W + i0 + dx;
         if (!hit[ray]) continue;
         const float *p = x + ((size_t)ray * K + k) * 3;
-        // positions into [0, 1] (NaN to 0), which level_setup's in-unit form
+        // positions into [0, kUnitTop] (NaN to 0), which level_setup's in-unit form
         // needs to keep every corner inside its level
-        const float x0 = p[0] >= 0.0f ? fminf(p[0], 1.0f) : 0.0f;
-        const float x1 = p[1] >= 0.0f ? fminf(p[1], 1.0f) : 0.0f;
-        const float x2 = p[2] >= 0.0f ? fminf(p[2], 1.0f) : 0.0f;
+        const float x0 = p[0] >= 0.0f ? fminf(p[0], mixrt::kUnitTop) : 0.0f;
+        const float x1 = p[1] >= 0.0f ? fminf(p[1], mixrt::kUnitTop) : 0.0f;
+        const float x2 = p[2] >= 0.0f ? fminf(p[2], mixrt::kUnitTop) : 0.0f;
         int l = 0;
         for (; l + kGroup <= n_dense; l += kGroup) acc ^= replay_group<EB, kGroup, true, MODE>(gp, l, x0, x1, x2);
         for (; l < n_dense; ++l) acc ^= replay_group<EB, 1, true, MODE>(gp, l, x0, x1, x2);

@@ -336,6 +336,13 @@ __device__ __forceinline__ void displacement(const RayParams &p, float u, float 
 // (identity inside the unit ball, (2 - 1/r) q/r outside), then the affine
 // map of [-2, 2]^3 onto the grid's unit cube.
 // --------------------------------------------------------------------------
+// The largest fp32 below 1.  x N, rounded to fp32, is then below N for every
+// N (N - N 2^-24 lies at least half a unit in the last place under N, and
+// where it is exactly half, N is not the nearer), so a level's voxel is the
+// integer part of the product and the fraction what is left: no clamp to the
+// last voxel and no conversion back.
+constexpr float kUnitTop = 0x1.fffffep-1f;
+
 __device__ __forceinline__ void contract_to_cube(float qx, float qy, float qz, float &x0,
                                                  float &x1, float &x2)
 {
@@ -345,9 +352,9 @@ __device__ __forceinline__ void contract_to_cube(float qx, float qy, float qz, f
         const float r = sqrtf(r2);
         s = (2.0f - 1.0f / r) / r;
     }
-    x0 = fminf(fmaxf((qx * s + 2.0f) * 0.25f, 0.0f), 1.0f);
-    x1 = fminf(fmaxf((qy * s + 2.0f) * 0.25f, 0.0f), 1.0f);
-    x2 = fminf(fmaxf((qz * s + 2.0f) * 0.25f, 0.0f), 1.0f);
+    x0 = fminf(fmaxf((qx * s + 2.0f) * 0.25f, 0.0f), kUnitTop);
+    x1 = fminf(fmaxf((qy * s + 2.0f) * 0.25f, 0.0f), kUnitTop);
+    x2 = fminf(fmaxf((qz * s + 2.0f) * 0.25f, 0.0f), kUnitTop);
     if (!(x0 == x0)) x0 = 0.0f;
     if (!(x1 == x1)) x1 = 0.0f;
     if (!(x2 == x2)) x2 = 0.0f;
@@ -601,14 +608,15 @@ constexpr uint32_t kPrimeZ = 805459861u;
 // level, as byte offsets into the level's table for entries of EB bytes.
 // Corner b has offset (b & 1, b >> 1 & 1, b >> 2 & 1).
 struct LevelSetup {
-    float cf[3];       // voxel corner c0 (integral values)
+    uint32_t c[3];     // voxel corner c0
     float fr[3];
     uint32_t off[8];   // entry index times EB
 };
 
-// IN_UNIT: the query is known to lie in [0, 1]^3 (the render path clamps it
-// there), so only the upper clamp of the voxel is needed.  Otherwise a
-// coordinate below 0 or NaN takes voxel 0, as the oracle does.
+// IN_UNIT: the query is known to lie in [0, kUnitTop]^3 (the render path
+// clamps it there), so the voxel needs no clamp.  Otherwise a coordinate
+// below 0 or NaN takes voxel 0 and one of N or more the last, as the oracle
+// does.
 //
 // The byte offsets are computed directly: shifting left distributes over
 // XOR and AND, so (h & (T - 1)) EB for a hash h = x ^ y pY ^ z pZ (mod 2^32)
@@ -619,41 +627,39 @@ __device__ __forceinline__ void level_setup(const GridParams &gp, int l, bool de
                                             float x1, float x2, LevelSetup &s)
 {
     static_assert(EB == 4 || EB == 8 || EB == 16, "entry size");
-    const uint32_t N = gp.N[l], T_mask = gp.T_mask;
     const float Nf = gp.Nf[l], top = gp.Ntop[l];
-    // p = x N rounded once to fp32, as the oracle takes it.  The empty asm
-    // keeps the compiler from fusing the product into p - c0 (which would
-    // skip that rounding); with it, p - c0 is exact (c0 <= p < c0 + 1), so the
-    // fractions equal the oracle's.
     float p[3] = {x0 * Nf, x1 * Nf, x2 * Nf};
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-        asm("" : "+v"(p[a]));
-    uint32_t c[3];
+    uint32_t *c = s.c;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         if (IN_UNIT) {
-            // 0 <= p <= N: truncation is the floor, clamped to N - 1 in
-            // integers (the float clamp would first have to quiet p)
-            c[a] = min((uint32_t)p[a], N - 1u);
-            s.cf[a] = (float)c[a];
+            // 0 <= p < N: truncation is the floor, and p minus it is exact
+            c[a] = (uint32_t)p[a];
+            s.fr[a] = __builtin_amdgcn_fractf(p[a]);
         } else {
+            // p = x N rounded once to fp32, as the oracle takes it.  The empty
+            // asm keeps the compiler from fusing the product into p - c0
+            // (which would skip that rounding); with it, p - c0 is exact
+            // (c0 <= p < c0 + 1), so the fractions equal the oracle's.
+            asm("" : "+v"(p[a]));
             // floor(min(p, N - 1)) = min(floor(p), N - 1), N - 1 integral
-            s.cf[a] = floorf(fminf(fmaxf(p[a], 0.0f), top));
-            c[a] = (uint32_t)s.cf[a];
+            const float cf = floorf(fminf(fmaxf(p[a], 0.0f), top));
+            c[a] = (uint32_t)cf;
+            s.fr[a] = p[a] - cf;
         }
-        s.fr[a] = p[a] - s.cf[a];
     }
     if (dense) {
-        const uint32_t s1 = N + 1u, s2 = s1 * s1;
-        const uint32_t base = c[0] * EB + c[1] * (s1 * EB) + c[2] * (s2 * EB);
+        // (strides below 2^24 bytes: the 24-bit multiply, which issues in a
+        // quarter of the 32-bit one's time)
+        const uint32_t s1 = gp.N[l] + 1u, s2 = s1 * s1;
+        const uint32_t base = c[0] * EB + __umul24(c[1], s1 * EB) + __umul24(c[2], s2 * EB);
 #pragma unroll
         for (int b = 0; b < 8; ++b)
             s.off[b] = base + ((b & 1) ? EB : 0u) + ((b & 2) ? s1 * EB : 0u) +
                        ((b & 4) ? s2 * EB : 0u);
     } else {
         constexpr uint32_t pY = kPrimeY * EB, pZ = kPrimeZ * EB;   // mod 2^32
-        const uint32_t mask = T_mask * EB;
+        const uint32_t mask = gp.T_mask * EB;
         const uint32_t hx0 = c[0] * EB, hx1 = hx0 + EB;
         const uint32_t hy0 = c[1] * pY, hy1 = hy0 + pY;
         const uint32_t hz0 = c[2] * pZ, hz1 = hz0 + pZ;

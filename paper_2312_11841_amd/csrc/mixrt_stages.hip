@@ -50,7 +50,7 @@ __global__ __launch_bounds__(kBlock) void hash_encode_kernel(GridParams gp, cons
         level_accumulate<F>(st, v, f);
         const int64_t sl = s * gp.L + l;
         if (out_corner)
-            for (int a = 0; a < 3; ++a) out_corner[sl * 3 + a] = (int32_t)st.cf[a];
+            for (int a = 0; a < 3; ++a) out_corner[sl * 3 + a] = (int32_t)st.c[a];
         if (out_idx)
             for (int b = 0; b < 8; ++b) out_idx[sl * 8 + b] = st.off[b] / eb;
         if (out_w)
