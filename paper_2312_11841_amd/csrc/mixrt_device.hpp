@@ -349,8 +349,13 @@ __device__ __forceinline__ void contract_to_cube(float qx, float qy, float qz, f
     const float r2 = qx * qx + qy * qy + qz * qz;
     float s = 1.0f;
     if (r2 > 1.0f) {
-        const float r = sqrtf(r2);
-        s = (2.0f - 1.0f / r) / r;
+        // (2 - 1/r) / r from 1/r alone: the hardware reciprocal square root
+        // and one Newton step, accurate to the last place or so, where a
+        // square root and two divisions take some 50 operations more.
+        // r2 = inf (a point beyond 1e19) scales to 0, as 1/r = 0 does.
+        const float y = __builtin_amdgcn_rsqf(r2);
+        const float inv = y + (0.5f * y) * fmaf(-(r2 * y), y, 1.0f);
+        s = r2 < INFINITY ? (2.0f - inv) * inv : 0.0f;
     }
     x0 = fminf(fmaxf((qx * s + 2.0f) * 0.25f, 0.0f), kUnitTop);
     x1 = fminf(fmaxf((qy * s + 2.0f) * 0.25f, 0.0f), kUnitTop);
