@@ -112,10 +112,13 @@ typedef struct {
                             features only; speed only, never a result): > 0
                             that many (hashed levels only), < 0 none, 0 the
                             library's choice (2 features: the three finest,
-                            five in rounds of one sample per ray, four when a
-                            level's table exceeds one XCD's L2 (eight at K >=
-                            8), among the hashed levels finer than a ray's
-                            sample spacing; 4 features: every hashed level
+                            up to seven at K < 4 as the pixels lie apart, five
+                            in rounds of one sample per ray (seven at K >= 8),
+                            both only in frames with a tile for every wave;
+                            four when a level's table exceeds one XCD's L2
+                            (eight at K >= 8); among the hashed levels finer
+                            than a ray's sample spacing; 4 features: every
+                            hashed level
                             when there are 8 or more in tables of 2^10 or
                             more entries, else none) */
 } mixrt_create_info;

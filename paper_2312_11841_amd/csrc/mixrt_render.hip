@@ -650,27 +650,34 @@ static int render_chunk(const RenderLaunch &L)
 }
 
 // First level whose x-neighbour corner pairs are gathered as 16-byte
-// blocks (gp.L: none; tables of 4-byte entries only).  By default the three
-// finest levels (when a level's table exceeds one XCD's L2, whose misses
-// scatter more: four, and at K >= 8 up to eight, which took the 8-view
-// 1080p batch from 12.51 to 12.03 ms while 8 MiB levels at 720p and K = 8
-// stayed within 0.2% and at K = 4 lost 2.6%; in rounds of one sample per
-// ray, whose lanes are 64 rays whose samples lie apart on more levels: five,
-// 1-3% faster at spacing 0.25 and K 4 to 16), among the hashed levels finer
-// than a ray's sample spacing (coarser levels hand a ray's neighbouring
-// samples the same lines, where a 4-byte gather is cheaper).  Measured against single-entry gathers
-// on every level: the finest 2 to 4 levels were 2-15% faster at 720p (K 1 to
-// 16, spacings 0.01 to 0.25, early termination or not) and 5-8% on the
-// 8-view 1080p batch (8 MiB levels; 4 levels 1.5% faster there than 3),
-// 1-5% slower only at K = 32 on a 4096-pixel-wide view; all hashed levels
-// (or every level finer than the spacing) were slower on most.
+// blocks (gp.L: none; tables of 4- and 8-byte entries).
+//
+// 4-byte entries: blocks pay on levels whose lanes touch lines of their own
+// (coarser ones hand neighbouring lanes the same lines, where a 4-byte gather
+// is cheaper), so among the hashed levels finer than a ray's sample spacing:
+//  - one to three samples per ray, whose lanes are neighbouring pixels: the
+//    levels whose cells are finer than the pixels' spacing at a distance of 8,
+//    3 to 7 of them.  Against always 3, 1280x720 at K = 1 / 2 / 3 went from
+//    118 / 171 / 243 us to 103 / 160 / 232, 640x360 at K = 1 from 59.6 to 56.0,
+//    1920x1080 from 187 to 171, 2560x1440 from 281 to 257, and a 4096x4096 view
+//    keeps 3 (7 there: 1.06 ms as with 3, and at K = 2 2.03 against 1.93).
+//    Frames with fewer tiles than the card holds waves keep 3: nothing hides
+//    the blocks' one level per batch there (320x180: 30.5 us with 3, 32.1 with
+//    7);
+//  - rounds of one sample per ray: 5, and 7 from K = 8 on in frames that fill
+//    the card (spacing 0.25 at K = 8 829 -> 819 us, at 0.1 826 -> 815, K = 16
+//    1825 -> 1823; K = 4 would lose 1.6%);
+//  - levels larger than one XCD's L2, whose misses scatter more: 4, and 8 from
+//    K = 8 on (the 8-view 1080p batch 10.95 ms with 4, 10.63 with 8);
+//  - else 3 (view720p 491 us with 3 to 5, 498 with 2, 502 with 6; opaque content
+//    300 with 3, 303 with 5).
+// 8-byte entries: every hashed level, with 8 or more of them in tables of at
+// least 2^10 entries.
 static int render_block_from(const RenderLaunch &L)
 {
     const int nl = L.gp.L;
     if (L.block_levels < 0) return nl;
     if (L.tf16 && L.F == 4) {
-        // 8-byte entries: every hashed level, with 8 or more of them in
-        // tables of at least 2^10 entries
         const int nd = L.gp.n_dense;
         if (L.block_levels > 0) return nl - L.block_levels > nd ? nl - L.block_levels : nd;
         return nl - nd >= 8 && L.gp.T_mask >= 1023u ? nd : nl;
@@ -679,13 +686,29 @@ static int render_block_from(const RenderLaunch &L)
     int lo = L.gp.n_dense;
     if (L.block_levels > 0) return nl - L.block_levels > lo ? nl - L.block_levels : lo;
     const int64_t level_bytes = ((int64_t)L.gp.T_mask + 1) * 4;
-    const int kFinest = level_bytes > L.l2_bytes ? (L.rp.K >= 8 ? 8 : 4)
-                        : render_chunk(L) == 1 ? 5 : 3;
+    const bool fills = tile_shape(kWave / L.rp.K, L.rp.views, L.rp.W, L.rp.H, 0).n_tiles >=
+                       3 * kWavesPerBlock * L.cus;
+    int finest = 3;
+    if (level_bytes > L.l2_bytes) {
+        finest = L.rp.K >= 8 ? 8 : 4;
+    } else if (L.rp.K < 4) {
+        if (fills) {
+            // a pixel at distance 8, in grid units inside the unit ball
+            float spacing = 8.0f;
+            for (int v = 0; v < L.rp.views; ++v) spacing = fminf(spacing, 2.0f * L.rp.cams[v].inv_f);
+            int finer = 0;
+            for (int l = 0; l < nl; ++l)
+                if ((float)L.gp.N[l] * spacing >= 1.0f) ++finer;
+            finest = finer < 3 ? 3 : finer > 7 ? 7 : finer;
+        }
+    } else if (render_chunk(L) == 1) {
+        finest = fills && L.rp.K >= 8 ? 7 : 5;
+    }
     if (L.rp.K > 1) {
         const int shared = levels_shared_by_samples(L);
         if (shared > lo) lo = shared;
     }
-    return nl - kFinest > lo ? nl - kFinest : (lo < nl ? lo : nl);
+    return nl - finest > lo ? nl - finest : (lo < nl ? lo : nl);
 }
 
 // Whether the x + 1 entries of straddling voxels are loaded after a level's
