@@ -105,7 +105,9 @@ typedef struct {
                             not a power of two, or coherent samples on levels
                             larger than one XCD's L2; otherwise rounds of 4, 2
                             or 1 as a ray's samples share the voxels of at
-                            least half, a quarter or fewer of the levels */
+                            least half, a quarter or fewer of the levels,
+                            doubled (up to all K at once) in frames whose
+                            rounds would leave most waves without a ray */
     int32_t block_levels; /* how many of the finest hash levels gather each
                             x-neighbour pair of corners as one aligned 16-byte
                             block holding both entries (tables of 2 or 4 fp16
@@ -118,9 +120,8 @@ typedef struct {
                             four when a level's table exceeds one XCD's L2
                             (eight at K >= 8); among the hashed levels finer
                             than a ray's sample spacing; 4 features: every
-                            hashed level
-                            when there are 8 or more in tables of 2^10 or
-                            more entries, else none) */
+                            hashed level when there are 8 or more in tables of
+                            2^10 or more entries, else none) */
 } mixrt_create_info;
 
 /* The coarse-mesh hit per pixel (Fig. 2 step 1): rasterisation output. */
@@ -272,7 +273,9 @@ typedef struct {
     int32_t blocks;      /* persistent grid, blocks of 256 threads */
     int32_t tile_stripe; /* tile-order stripe width in tiles (the image's tile
                             columns for row-major order) */
-    int32_t chunk;       /* samples per ray per round (0: all K at once) */
+    int32_t chunk;       /* samples per ray per round (0: all K at once); with
+                            the library's choice, a frame with too few tiles
+                            for that takes more at once, up to all K */
     int32_t block_from;  /* first hash level whose x-neighbour corner pairs
                             are gathered as 16-byte blocks (L: none) */
     int32_t hash_batch;  /* hashed levels per batch of gathers (2 or 4) */

@@ -649,6 +649,26 @@ static int render_chunk(const RenderLaunch &L)
     return c;
 }
 
+// The samples per ray per round that a frame is launched with: by default
+// twice render_chunk's as often as it takes for half the waves to get a run
+// of K / C tiles (the tile path once that takes all K samples).  With fewer
+// runs, most of the card waits while a few waves go round after round.
+// Measured at K = 8, translucent / opaque content, us: 160x90 at spacing 0.25
+// 289 / 56 in rounds of 1, 44 / 43 in the tile path, at 0.01 52 / 40 in rounds
+// of 4, 32 / 31; 320x180 at 0.25 262 / 53 in rounds of 1, 133 / 43 of 2 (119 /
+// 64 of 4, so no further); 640x360, a run for every wave, 353 / 74 of 1 and
+// 344 / 102 of 2.  64x64 at K = 4 24.4 in rounds of 1, 11.2 in the tile path.
+static int render_round(const RenderLaunch &L)
+{
+    int c = render_chunk(L);
+    if (L.chunk != 0 || c == 0) return c;
+    const int K = L.rp.K;
+    const int64_t n = tile_shape(kWave / K, L.rp.views, L.rp.W, L.rp.H, 0).n_tiles;
+    const int64_t waves = 3 * kWavesPerBlock * (int64_t)L.cus;
+    while (c < K && 2 * n * c < K * waves) c *= 2;
+    return c < K ? c : 0;
+}
+
 // First level whose x-neighbour corner pairs are gathered as 16-byte
 // blocks (gp.L: none; tables of 4- and 8-byte entries).
 //
@@ -721,7 +741,7 @@ static int render_block_from(const RenderLaunch &L)
 static bool render_far_last(const RenderLaunch &L)
 {
     const int64_t level_bytes = ((int64_t)L.gp.T_mask + 1) * 4;
-    return render_chunk(L) != 1 && level_bytes <= L.l2_bytes;
+    return render_round(L) != 1 && level_bytes <= L.l2_bytes;
 }
 
 // Hashed levels per batch of gathers: 4 for entries of 8 or more bytes
@@ -790,7 +810,7 @@ hipError_t launch_render(const RenderLaunch &L0, hipStream_t stream)
     if (MIXRT_RENDER_MATCH(a, b, c, d, e, f)) {                                                \
         int64_t blocks;                                                                        \
         int stripe;                                                                            \
-        const int chunk = render_chunk(L);                                                     \
+        const int chunk = render_round(L);                                                     \
         unsigned int *work = render_claims(L) ? L.work : nullptr;                              \
         render_shape(L, render_resident<a, b, c, d, e, f>(chunk > 0), blocks, stripe);         \
         if (chunk > 0)                                                                         \
@@ -835,7 +855,7 @@ hipError_t render_launch_shape(const RenderLaunch &L, int *blocks, int *stripe, 
     if (MIXRT_RENDER_MATCH(a, b, c, d, e, f)) {                                                \
         int64_t nb;                                                                            \
         *chunk = render_chunk(L);                                                              \
-        render_shape(L, render_resident<a, b, c, d, e, f>(*chunk > 0), nb, *stripe);          \
+        render_shape(L, render_resident<a, b, c, d, e, f>(render_round(L) > 0), nb, *stripe); \
         *blocks = (int)nb;                                                                     \
         return hipSuccess;                                                                     \
     }
