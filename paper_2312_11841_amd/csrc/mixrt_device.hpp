@@ -847,7 +847,7 @@ __device__ __forceinline__ const void *level_base(const GridParams &g, int l, in
 // G consecutive levels starting at l0, all of one kind (dense or hashed):
 // every corner load of the group is issued before any interpolation, so a
 // wave keeps 4G (dense) or 8G (hashed) gathers in flight.
-template <int F, bool F16, int G, bool DENSE, int FORM = kEntries>
+template <int F, bool F16, int G, bool DENSE, int FORM = kEntries, bool IN_UNIT = true>
 __device__ __forceinline__ void hash_group(const GridParams &gp, int l0, float x0, float x1,
                                            float x2, float (*feat)[F])
 {
@@ -855,7 +855,7 @@ __device__ __forceinline__ void hash_group(const GridParams &gp, int l0, float x
     float v[G][8][F];
 #pragma unroll
     for (int g = 0; g < G; ++g)
-        level_setup<TableEntry<F, F16>::kBytes, true>(gp, l0 + g, DENSE, x0, x1, x2, s[g]);
+        level_setup<TableEntry<F, F16>::kBytes, IN_UNIT>(gp, l0 + g, DENSE, x0, x1, x2, s[g]);
 #pragma unroll
     for (int g = 0; g < G; ++g)
         level_fetch<F, F16, DENSE, FORM>(level_base(gp, l0 + g, F, F16), s[g], v[g]);

@@ -60,6 +60,94 @@ __global__ __launch_bounds__(kBlock) void hash_encode_kernel(GridParams gp, cons
     }
 }
 
+// The features alone, which is what a program that keeps them asks for.  A
+// wave takes 64 queries, two levels' gathers in flight, and collects up to 32
+// features of each in LDS; they leave in rows of 16-byte stores past the
+// caches (written once, and the table's lines stay).  Written from the lanes
+// as they come, one 4-byte store per feature touches 64 lines and most lines
+// come back to memory in pieces: 473 us for 1.84 M queries of 16 levels
+// against 148 (236 MB written).  Neighbouring waves go to one XCD, whose L2
+// serves the voxels they share.
+// Block -> logical block: runs of `run` consecutive blocks go to one XCD
+// (hardware block b runs on XCD b mod 8), the XCDs' runs one after another.
+// The grid is a multiple of 8 run.
+__device__ __forceinline__ int xcd_run_block(int b, int run)
+{
+    const int turn = b / (8 * run), i = b - turn * (8 * run);
+    return turn * (8 * run) + (i & 7) * run + (i >> 3);
+}
+
+constexpr int kFeatCols = 32;               // features collected at a time
+constexpr int kFeatRow = kFeatCols + 4;     // LDS row, 16-byte multiple
+
+template <int F, bool TF16, int G, bool DENSE, int FORM>
+__device__ __forceinline__ void features_of(const GridParams &gp, int l, float x0, float x1,
+                                            float x2, float *col)
+{
+    float f[G][F];
+    hash_group<F, TF16, G, DENSE, FORM, false>(gp, l, x0, x1, x2, f);
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int i = 0; i < F; ++i) col[g * F + i] = f[g][i];
+}
+
+template <int F, bool TF16>
+__global__ __launch_bounds__(kBlock) void hash_features_kernel(GridParams gp,
+                                                               const float *__restrict__ x,
+                                                               int64_t n, int wide, int run,
+                                                               float *__restrict__ out)
+{
+    __shared__ __attribute__((aligned(16))) float s_f[kWavesPerBlock][kWave * kFeatRow];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t base =
+        ((int64_t)xcd_run_block((int)blockIdx.x, run) * kWavesPerBlock + wv) * kWave;
+    if (base >= n) return;
+    const int rows = n - base < kWave ? (int)(n - base) : kWave;
+    float x0 = 0.0f, x1 = 0.0f, x2 = 0.0f;   // (lanes past n: voxel 0, never stored)
+    if (lane < rows) {
+        const float *p = x + 3 * (base + lane);
+        x0 = p[0];
+        x1 = p[1];
+        x2 = p[2];
+    }
+    float *const buf = s_f[wv];
+    const int L = gp.L, LF = L * F;
+    constexpr int kLevels = kFeatCols / F;
+    for (int l0 = 0; l0 < L; l0 += kLevels) {
+        const int l1 = l0 + kLevels < L ? l0 + kLevels : L;
+        const int ld = gp.n_dense < l1 ? gp.n_dense : l1;
+        const int lb = gp.block_from < l1 ? gp.block_from : l1;
+        float *const row = buf + lane * kFeatRow - l0 * F;
+        int l = l0;
+        for (; l + 2 <= ld; l += 2) features_of<F, TF16, 2, true, kEntries>(gp, l, x0, x1, x2, row + l * F);
+        for (; l < ld; ++l) features_of<F, TF16, 1, true, kEntries>(gp, l, x0, x1, x2, row + l * F);
+        for (; l + 2 <= lb; l += 2) features_of<F, TF16, 2, false, kEntries>(gp, l, x0, x1, x2, row + l * F);
+        for (; l < lb; ++l) features_of<F, TF16, 1, false, kEntries>(gp, l, x0, x1, x2, row + l * F);
+        if constexpr (kBlockPairs<F, TF16> || kBlockPairs8<F, TF16>)
+            for (; l < l1; ++l)
+                features_of<F, TF16, 1, false, kBlocksWithFar>(gp, l, x0, x1, x2, row + l * F);
+        wave_lds_sync();
+        const int cols = (l1 - l0) * F;
+        float *const o = out + base * LF + l0 * F;
+        if (wide) {
+            const int per = cols / 4;   // 16-byte chunks per row
+            for (int e = lane; e < rows * per; e += kWave) {
+                const int r = e / per, c = 4 * (e - r * per);
+                __builtin_nontemporal_store(*(const f4 *)(buf + r * kFeatRow + c),
+                                            (f4 *)(o + (int64_t)r * LF + c));
+            }
+        } else {
+            for (int e = lane; e < rows * cols; e += kWave) {
+                const int r = e / cols, c = e - r * cols;
+                __builtin_nontemporal_store(buf[r * kFeatRow + c], o + (int64_t)r * LF + c);
+            }
+        }
+        wave_lds_sync();
+    }
+}
+
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"   // M0 is clobbered on purpose
 // One 16-byte chunk per lane straight from global memory into LDS
@@ -248,6 +336,33 @@ hipError_t launch_hash_encode(const GridParams &gp, int F, bool tf16, const floa
                               int32_t *oc, uint32_t *oi, float *ow, float *of, hipStream_t stream)
 {
     if (n == 0) return hipSuccess;
+    if (of && !oc && !oi && !ow) {
+        GridParams g = gp;
+        // the finest hashed levels in 16-byte blocks: 6 of 4-byte entries, 3 of
+        // 8-byte ones (the 640x360 view's 1.84 M queries 177 us with 3, 173 with
+        // 6 and with 9; Tab. 3's 8 levels of 8-byte entries 99.8 with 3, 101.8
+        // with 6)
+        const int from = tf16 ? g.L - (F == 2 ? 6 : 3) : g.L;
+        g.block_from = from > g.n_dense ? from : g.n_dense;
+        const int wide = (g.L * F) % 4 == 0 && ((uintptr_t)of & 15) == 0;
+        const int64_t nb = (n + kBlock - 1) / kBlock;
+        // Runs of 64 blocks keep neighbouring queries in one L2 (1280x720 queries
+        // of one sample per pixel 167 us without runs, 150 in runs of 16, 143 of
+        // 64), 8 or more of them per XCD keep the XCDs evenly loaded (one eighth
+        // of 1.84 M queries each: 204 us against 168)
+        const int64_t run = nb / 64 < 1 ? 1 : nb / 64 > 64 ? 64 : nb / 64;
+        const dim3 grid((unsigned)((nb + 8 * run - 1) / (8 * run) * (8 * run)));
+#define LAUNCH(FF, TT)                                                                         \
+    hipLaunchKernelGGL((hash_features_kernel<FF, TT>), grid, dim3(kBlock), 0, stream, g, x, n,  \
+                       wide, (int)run, of)
+        if (F == 2 && tf16) LAUNCH(2, true);
+        else if (F == 2) LAUNCH(2, false);
+        else if (F == 4 && tf16) LAUNCH(4, true);
+        else if (F == 4) LAUNCH(4, false);
+        else return hipErrorInvalidValue;
+#undef LAUNCH
+        return hipGetLastError();
+    }
     const dim3 grid((unsigned)((n + kBlock - 1) / kBlock));
 #define LAUNCH(FF, TT)                                                                         \
     hipLaunchKernelGGL((hash_encode_kernel<FF, TT>), grid, dim3(kBlock), 0, stream, gp, x, n, oc, \

@@ -1,0 +1,144 @@
+"""The stage kernels and the render's launch rules at the sizes where they can
+go wrong: ragged tails of their tiles, rows that are not whole 16-byte chunks,
+outputs off a 16-byte boundary, blocks that cross rows and views, frames too
+small for rounds, and samples on the far faces of the grid's cube."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2312_11841_amd import mixrt, synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print(*a, flush=True)
+
+
+@pytest.fixture(scope="module")
+def R():
+    r = mixrt.Renderer(0, sync_check=True)
+    yield r
+    r.close()
+
+
+def _positions(rng, n):
+    """Random positions with the cube's corners, the largest float below 1 and
+    points just outside among them."""
+    x = rng.random((n, 3), dtype=np.float32)
+    edge = np.array([0.0, 1.0, np.nextafter(np.float32(1), np.float32(0)), 0.5, -0.25, 1.5],
+                    np.float32)
+    m = min(n, 64)
+    x[:m] = edge[rng.integers(0, len(edge), (m, 3))]
+    return x
+
+
+# (L, F, table dtype, log2_T, N_min, N_max): 32, 16 and fewer features at a
+# time, rows of 4, 6, 10 and 128 floats, dense levels only, hashed only
+GRIDS = [(16, 2, "f16", 14, 4, 512), (3, 2, "f16", 8, 16, 64), (5, 2, "f32", 12, 2, 300),
+         (1, 4, "f16", 10, 100, 100), (32, 4, "f16", 8, 3, 4000), (9, 4, "f32", 6, 1, 90),
+         (18, 2, "f16", 18, 2, 40)]
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1000, 70001])
+@pytest.mark.parametrize("grid", GRIDS, ids=lambda g: "L%d_F%d_%s_T%d" % g[:4])
+def test_features_alone_equal_the_full_encoding(R, grid, n):
+    """Asked for alone the features come from another kernel; they are the
+    same sums of the same entries, bit for bit, also where the output starts
+    off a 16-byte boundary."""
+    L, F, dt, log2_T, n_min, n_max = grid
+    say("features", grid, n)
+    rng = np.random.default_rng(n + L)
+    table = rng.uniform(-1, 1, (L, 1 << log2_T, F)).astype(np.float16 if dt == "f16" else np.float32)
+    g = mixrt.make_grid(torch.from_numpy(table).cuda(), n_min, n_max)
+    x = torch.from_numpy(_positions(rng, n)).cuda()
+    full = R.hash_encode(g, x)["feat"].cpu().numpy()
+    alone = R.hash_encode(g, x, want=("feat",))["feat"].cpu().numpy()
+    assert np.array_equal(alone, full, equal_nan=True)
+    out = torch.full((n * L * F + 3,), 7.0, device="cuda")
+    rc = mixrt.lib().mixrt_debug_hash_encode(R._h, C.byref(g), x.data_ptr(), n, None, None, None,
+                                             out.data_ptr() + 4)
+    assert rc == mixrt.MIXRT_OK
+    got = out.cpu().numpy()
+    assert np.array_equal(got[1:-2].reshape(n, L * F), full, equal_nan=True)
+    assert got[0] == 7.0 and (got[-2:] == 7.0).all()   # nothing around it
+
+
+@pytest.mark.parametrize("rays", [1, 63, 64, 65, 257])
+@pytest.mark.parametrize("K", [1, 2, 7, 8, 9, 16, 64])
+def test_composite_tails(R, K, rays):
+    """Chunks of 8 samples over 64 rays: every remainder of both, rays that
+    stop early and rays that never do (the bar of the other composite test)."""
+    say("composite", K, rays)
+    rng = np.random.default_rng(K * 1000 + rays)
+    s = rng.random((rays, K, 4), dtype=np.float32)
+    s[..., 0] = np.exp(rng.uniform(-3, 3, (rays, 1))) * s[..., 0]
+    s[::7, K // 2, 0] = np.inf
+    bg, delta = (0.2, 0.4, 0.6), 0.3
+    for t_term in (0.0, 1e-2):
+        smp = mixrt.make_sampling(K, delta, t_term)
+        got = R.composite(torch.from_numpy(s).cuda(), smp, bg).cpu().numpy()
+        ref = oracle.composite(s.astype(np.float64), delta, bg)
+        assert np.abs(got - ref).max() <= 1e-5 + t_term
+
+
+@pytest.mark.parametrize("views,W,H,K", [(1, 1, 1, 64), (3, 3, 5, 33), (2, 9, 4, 33), (3, 40, 3, 5),
+                                         (2, 300, 2, 1), (4, 7, 7, 8)])
+@pytest.mark.parametrize("base", [synth.TINY64_DENSE, synth.TINY64_VEC3], ids=lambda c: c.name)
+def test_ray_setup_blocks_across_rows_and_views(R, base, views, W, H, K):
+    """Blocks of whole rays whose pixels cross rows and views, rows shorter
+    than a block's rays, and a ragged last block."""
+    cfg = base.replace(name="ragged", views=views, W=W, H=H, K=K, delta=0.05)
+    say("ray_setup", cfg.disp, views, W, H, K)
+    sc = synth.make_scene(cfg)
+    sc.g0.reshape(-1, 4)[::5, 0] = -1.0
+    ds = mixrt.DeviceScene.from_scene(sc, "cuda:0")
+    x, hit = R.ray_setup(ds)
+    _, xd, hito = oracle.OracleScene(sc).pixel_samples(np.arange(cfg.rays))
+    assert np.array_equal(hit.cpu().numpy(), hito)
+    assert np.abs(x.cpu().numpy() - xd).max() <= 2e-5   # as test_ray_setup in test_gpu_parity
+
+
+@pytest.mark.parametrize("W,H", [(16, 16), (64, 64), (161, 90), (240, 135)])
+@pytest.mark.parametrize("K,delta", [(4, 0.25), (8, 0.25), (8, 0.05), (8, 0.01), (32, 0.1)])
+def test_small_frames_render_the_same_in_every_round_size(W, H, K, delta):
+    """Frames of few tiles take more samples at once by default; every round
+    size and the tile path give the same bits."""
+    cfg = synth.VIEW720P_DENSE.replace(name="small", W=W, H=H, K=K, delta=delta, log2_T=12,
+                                       N_max=1024, tex_R=64)
+    say("small frame", W, H, K, delta)
+    ds = mixrt.DeviceScene.from_scene(synth.make_scene(cfg), "cuda:0")
+    frames = []
+    for chunk in (0, -1, 1, 2, K):
+        r = mixrt.Renderer(0, sync_check=True, early_stop_chunk=chunk)
+        frames.append(r.render(ds).cpu().numpy())
+        r.close()
+    for f in frames[1:]:
+        assert np.array_equal(f, frames[0])
+
+
+@pytest.mark.parametrize("K", [1, 4, 8])
+def test_samples_on_the_far_faces_of_the_cube(R, K):
+    """Points so far away that they contract onto the ball's surface: along an
+    axis the cube coordinate rounds to 1, which takes the last voxel and its
+    far corner, as the oracle does (frame bar of the parity tests)."""
+    cfg = synth.TINY64_DENSE.replace(name="far", W=33, H=33, K=K, delta=0.5, disp="none")
+    sc = synth.make_scene(cfg)
+    rng = np.random.default_rng(K)
+    t = 10.0 ** rng.uniform(3, 12, cfg.rays)
+    t[cfg.rays // 2] = 1e12                              # the pixel on the axis
+    sc.g0[..., 0] = t.reshape(sc.g0.shape[:3])
+    for axis in ((0, 0, 1), (1, 0, 0), (0, 1, 0)):       # looking along +axis
+        b = np.array(axis, np.float64)                   # -R[:, 2]
+        u = np.roll(b, 1)
+        sc.cams[0, :12] = np.concatenate([np.stack([np.cross(u, -b), u, -b], 1),
+                                          np.zeros((3, 1))], 1).reshape(-1)
+        ds = mixrt.DeviceScene.from_scene(sc, "cuda:0")
+        x, _ = R.ray_setup(ds)
+        assert float(x.max()) < 1.0 and float(x.min()) >= 0.0
+        got = R.render(ds).cpu().numpy()
+        ref = oracle.OracleScene(sc).render_pixels(np.arange(cfg.rays))
+        assert np.abs(got - ref).max() <= 2e-3
