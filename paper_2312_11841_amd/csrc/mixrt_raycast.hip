@@ -7,10 +7,22 @@
 // the nearest occupied cell sits in a cube of (2D-1)^3 empty cells, so the ray
 // moves straight to the face where it leaves that cube.
 //
-// Launch shape: one 256-lane block per 16 x 16 pixel tile, each wave an 8 x 8
-// quadrant, so the 64 rays of a wave cross nearly the same cells and their
-// cell-list and triangle loads coalesce into few cache lines.  Neighbouring
-// tiles are mapped to the same XCD so that its L2 holds the cells they share.
+// Launch shape: one wave per 8 x 8 pixel tile, so its 64 rays cross nearly the
+// same cells and their cell-list and triangle loads coalesce into few cache
+// lines; blocks of one wave, so that a finished wave's place is taken at once
+// (the card is a quarter full on average: a few waves graze objects for five
+// times the mean).  Neighbouring tiles are mapped to the same XCD so that its
+// L2 holds the cells they share.
+//
+// What bounds it: VALU issue on large frames, the slowest waves' chain of
+// loads and steps on small ones.  Measured (us, 499,712 triangles; 1280x720 /
+// 64x64 / 2560x1440): 198 / 166 / 350 with 256-lane blocks and a world-space
+// walk of two forms (step and leap, which a wave ran one after the other);
+// 196 / 149 / 354 with blocks of one wave; 154 / 109 / 300 with the walk in
+// units of cells and one form.  Without effect: one byte per cell in bricks of
+// 8 x 4 x 4 cells for the walk (154 / 110 / 296), the next cell's record loaded
+// before the tests (196 / 163 / 353 on 256-lane blocks), two records ahead (200
+// / 171 / 385: registers).
 #include "mixrt_common.hpp"
 #include "mixrt_mesh.hpp"
 
@@ -18,7 +30,7 @@ namespace mixrt {
 
 namespace {
 
-constexpr int kTile = 16;
+constexpr int kTile = 8;
 constexpr float kInf = __builtin_inff();
 
 struct Hit {
@@ -64,70 +76,50 @@ __device__ __forceinline__ void test_tri(const Tri &T, uint32_t r, const Ray &ra
     }
 }
 
-// Distance to the next cell face on one axis from cell c.
-__device__ __forceinline__ float next_face(const MeshGridK &g, int a, int c, int step, float o,
-                                           float inv)
-{
-    return (g.lo[a] + (float)(c + (step > 0)) * g.cell[a] - o) * inv;
-}
-
-// The walk's state: current cell, step direction and the distance to the
-// next face on each axis.
+// The walk, in units of cells: the ray is o + t d with o and d scaled by the
+// cell size (t is unchanged), a cell is its integer coordinates held as
+// floats, and tn[a] = (c + face[a]) inv[a] is the distance to its next face on
+// axis a (face holds -o and which of the two faces; inf where the ray does
+// not move on the axis).  Scaled coordinates err by about 1e-5 of a cell,
+// triangles are listed in cells padded by 1/500.
 struct Walk {
-    int c[3], st[3];
-    float tn[3];
+    float o[3], d[3], inv[3], face[3], st[3];
+    float c[3], tn[3];
 };
 
-// Move to the next cell: one DDA step (leap <= 1), or out of the empty cube
-// c +- (leap - 1) through its nearest face, where that axis moves leap cells
-// and the others go to the cell holding the exit point, kept inside the cube
-// and never moved backwards.  False once the ray leaves the grid.
-__device__ __forceinline__ bool advance(const MeshGridK &g, const float o[3], const float d[3],
-                                        const float inv[3], int leap, Walk &w)
+__device__ __forceinline__ void faces(Walk &w)
 {
-    if (leap <= 1) {
-        const int ax = (w.tn[0] <= w.tn[1] && w.tn[0] <= w.tn[2]) ? 0 : (w.tn[1] <= w.tn[2] ? 1 : 2);
-        int ca = 0;
 #pragma unroll
-        for (int a = 0; a < 3; ++a)
-            if (a == ax) ca = w.c[a] + w.st[a];
-        if (ca < 0 || ca >= g.n[ax]) return false;
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-            if (a == ax) {
-                w.c[a] = ca;
-                w.tn[a] = next_face(g, a, ca, w.st[a], o[a], inv[a]);
-            }
-        return true;
-    }
-    float te[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-        te[a] = w.st[a] ? next_face(g, a, w.c[a] + w.st[a] * (leap - 1), w.st[a], o[a], inv[a]) : kInf;
-    const int ax = (te[0] <= te[1] && te[0] <= te[2]) ? 0 : (te[1] <= te[2] ? 1 : 2);
-    const float t = fminf(te[0], fminf(te[1], te[2]));
-    bool out = false;
+    for (int a = 0; a < 3; ++a) w.tn[a] = (w.c[a] + w.face[a]) * w.inv[a];
+}
+
+// Move out of the empty cube c +- (leap - 1) (for leap = 1 the cell itself)
+// through its nearest face: that axis moves leap cells, the others go to the
+// cell holding the exit point, kept inside the cube, so never backwards.  One
+// form for both cases: lanes that leap and lanes that step move together.
+// False once the ray leaves the grid.
+__device__ __forceinline__ bool advance(const MeshGridK &g, int leap, Walk &w)
+{
+    const float m = (float)(leap - 1);
+    float far[3], te[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        int ca;
-        if (a == ax) {
-            ca = w.c[a] + w.st[a] * leap;
-        } else if (w.st[a] == 0) {
-            ca = w.c[a];
-        } else {
-            ca = (int)floorf((o[a] + t * d[a] - g.lo[a]) * g.inv_cell[a]);
-            const int lo_a = w.st[a] > 0 ? w.c[a] : w.c[a] - (leap - 1);
-            const int hi_a = w.st[a] < 0 ? w.c[a] : w.c[a] + (leap - 1);
-            ca = min(max(ca, lo_a), hi_a);
-        }
-        out |= ca < 0 || ca >= g.n[a];
-        w.c[a] = ca;
+        far[a] = w.c[a] + w.st[a] * m;
+        te[a] = (far[a] + w.face[a]) * w.inv[a];
     }
-    if (out) return false;
+    const float t = fminf(te[0], fminf(te[1], te[2]));
+    const bool x = te[0] <= te[1] && te[0] <= te[2];
+    const bool y = !x && te[1] <= te[2];
+    bool in = true;
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
-        w.tn[a] = w.st[a] ? next_face(g, a, w.c[a], w.st[a], o[a], inv[a]) : kInf;
-    return true;
+    for (int a = 0; a < 3; ++a) {
+        const float at = floorf(w.o[a] + t * w.d[a]);
+        const bool exit = a == 0 ? x : a == 1 ? y : !x && !y;
+        w.c[a] = exit ? far[a] + w.st[a] : __builtin_amdgcn_fmed3f(at, w.c[a], far[a]);
+        in = in && w.c[a] >= 0.0f && w.c[a] < (float)g.n[a];
+    }
+    faces(w);
+    return in;
 }
 
 __device__ __forceinline__ uint2 cell_rec(const MeshGridK &g, const Walk &w)
@@ -140,23 +132,26 @@ __device__ __forceinline__ Hit cast(const MeshGridK &g, const Ray &r)
 {
     Hit h{kInf, 0.0f, 0.0f, INT32_MAX, 0u};
     const float o[3] = {r.ox, r.oy, r.oz}, d[3] = {r.dx, r.dy, r.dz};
-    float inv[3], t0 = 0.0f, t1 = kInf;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        inv[a] = 1.0f / d[a];
-        const float ta = (g.lo[a] - o[a]) * inv[a], tb = (g.hi[a] - o[a]) * inv[a];
-        t0 = fmaxf(t0, fminf(ta, tb));
-        t1 = fminf(t1, fmaxf(ta, tb));
-    }
-    if (!(t0 <= t1) || !(t0 < kInf)) return h;
+    float t0 = 0.0f, t1 = kInf;
     Walk w;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const int ca = (int)floorf((o[a] + t0 * d[a] - g.lo[a]) * g.inv_cell[a]);
-        w.c[a] = min(max(ca, 0), g.n[a] - 1);
-        w.st[a] = d[a] > 0.0f ? 1 : (d[a] < 0.0f ? -1 : 0);
-        w.tn[a] = w.st[a] ? next_face(g, a, w.c[a], w.st[a], o[a], inv[a]) : kInf;
+        const float inv = 1.0f / d[a];
+        const float ta = (g.lo[a] - o[a]) * inv, tb = (g.hi[a] - o[a]) * inv;
+        t0 = fmaxf(t0, fminf(ta, tb));
+        t1 = fminf(t1, fmaxf(ta, tb));
+        w.o[a] = (o[a] - g.lo[a]) * g.inv_cell[a];
+        w.d[a] = d[a] * g.inv_cell[a];
+        const bool moves = d[a] > 0.0f || d[a] < 0.0f;
+        w.st[a] = moves ? copysignf(1.0f, d[a]) : 0.0f;
+        w.inv[a] = moves ? inv * g.cell[a] : 1.0f;
+        w.face[a] = moves ? (d[a] > 0.0f ? 1.0f : 0.0f) - w.o[a] : kInf;
     }
+    if (!(t0 <= t1) || !(t0 < kInf)) return h;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        w.c[a] = fminf(fmaxf(floorf(w.o[a] + t0 * w.d[a]), 0.0f), (float)(g.n[a] - 1));
+    faces(w);
     // Every move goes at least one cell along the ray's direction on some
     // axis and never back on any, so the walk leaves the grid within
     // nx + ny + nz moves; the counter bounds it whatever the rounding.
@@ -167,7 +162,7 @@ __device__ __forceinline__ Hit cast(const MeshGridK &g, const Ray &r)
         // triangles, so that the lanes of a wave test triangles together.
         bool alive = true;
         while (rec.y == 0) {
-            if (--steps <= 0 || !advance(g, o, d, inv, (int)rec.x, w)) {
+            if (--steps <= 0 || !advance(g, (int)rec.x, w)) {
                 alive = false;
                 break;
             }
@@ -184,22 +179,22 @@ __device__ __forceinline__ Hit cast(const MeshGridK &g, const Ray &r)
             T = nT;
         }
         if (h.t <= fminf(w.tn[0], fminf(w.tn[1], w.tn[2]))) break;
-        if (--steps <= 0 || !advance(g, o, d, inv, 1, w)) break;
+        if (--steps <= 0 || !advance(g, 1, w)) break;
         rec = cell_rec(g, w);
     }
     return h;
 }
 
-__global__ __launch_bounds__(kBlock) void raycast_kernel(const RaycastLaunch L)
+__global__ __launch_bounds__(64) void raycast_kernel(const RaycastLaunch L)
 {
     const int tiles_x = (L.W + kTile - 1) / kTile, tiles_y = (L.H + kTile - 1) / kTile;
     const int per_view = tiles_x * tiles_y;
     const int b = xcd_logical_block((int)blockIdx.x, (int)gridDim.x);
     const int view = b / per_view, rem = b - view * per_view;
     const int ty = rem / tiles_x, tx = rem - ty * tiles_x;
-    const int w = (int)threadIdx.x >> 6, l = (int)threadIdx.x & 63;
-    const int i = tx * kTile + (w & 1) * 8 + (l & 7);
-    const int j = ty * kTile + (w >> 1) * 8 + (l >> 3);
+    const int l = (int)threadIdx.x & 63;
+    const int i = tx * kTile + (l & 7);
+    const int j = ty * kTile + (l >> 3);
     if (i >= L.W || j >= L.H) return;
     const Ray r = camera_ray(L.cams[view], L.W, L.H, (uint32_t)i, (uint32_t)j);
     const Hit h = cast(L.grid, r);
@@ -229,7 +224,7 @@ __global__ __launch_bounds__(kBlock) void raycast_kernel(const RaycastLaunch L)
 hipError_t launch_raycast(const RaycastLaunch &L, hipStream_t stream)
 {
     const int tiles = ((L.W + kTile - 1) / kTile) * ((L.H + kTile - 1) / kTile) * L.views;
-    hipLaunchKernelGGL(raycast_kernel, dim3(tiles), dim3(kBlock), 0, stream, L);
+    hipLaunchKernelGGL(raycast_kernel, dim3(tiles), dim3(64), 0, stream, L);
     return hipGetLastError();
 }
 
