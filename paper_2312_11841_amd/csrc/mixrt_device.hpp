@@ -21,6 +21,7 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 // had its second element read back as the first by this compiler, and
 // structs get split into single-dword loads.)
 typedef uint64_t u64a4 __attribute__((aligned(4)));
+typedef uint16_t u16a1 __attribute__((aligned(1)));
 typedef unsigned __int128 u128a8 __attribute__((aligned(8)));
 
 __device__ __forceinline__ h2 word_h2(uint32_t w) { return __builtin_bit_cast(h2, w); }
@@ -173,6 +174,7 @@ __device__ __forceinline__ float tex_elem(uint8_t e, float qs, float qo)
 struct Bilinear {
     int64_t t[4];   // element offsets of the 4 taps' texels (times C)
     float w[4];
+    int col;        // column of the first tap
 };
 
 __device__ __forceinline__ Bilinear bilinear_taps(int R, int C, float u, float v)
@@ -190,6 +192,7 @@ __device__ __forceinline__ Bilinear bilinear_taps(int R, int C, float u, float v
     const int ia0 = min(max(i0, 0), R - 1), ia1 = min(max(i0 + 1, 0), R - 1);
     const int jb0 = min(max(j0, 0), R - 1), jb1 = min(max(j0 + 1, 0), R - 1);
     Bilinear B;
+    B.col = ia0;
     B.t[0] = ((int64_t)jb0 * R + ia0) * C;
     B.t[1] = ((int64_t)jb0 * R + ia1) * C;
     B.t[2] = ((int64_t)jb1 * R + ia0) * C;
@@ -245,6 +248,43 @@ __device__ __forceinline__ float bilinear_elem(const XT *tex, const Bilinear &B,
     return m;
 }
 
+// Keeps the loads before it before those after it.  The two entries of an
+// x-neighbour pair mostly share a line, and the vector L1, which the waves of
+// a CU fill with 64 lines per gather, holds it for few gathers: with the
+// compiler free to mix the levels of a batch, the deployed grid's 1280x720
+// frame took 105 us, with the levels apart 97.8, and with every pair's loads
+// next to each other 91.6 (view720p 494, 491, 488.5; spread samples 854, 848,
+// 841).
+__device__ __forceinline__ void load_order() { asm volatile("" ::: "memory"); }
+
+// The scale map m_s at (u, v).  8-bit maps read a row's two taps, neighbouring
+// bytes, in one 2-byte load (at the right edge the pair ending there), two
+// gathers instead of four.
+template <typename XT>
+__device__ __forceinline__ float scale_map(const RayParams &p, float u, float v)
+{
+    const Bilinear B = bilinear_taps(p.tex_R, 1, u, v);
+    const TapWeights<XT> tw(B, p.q_scale[1], p.q_offset[1]);
+    const XT *map = (const XT *)p.tex_scale;
+    if (std::is_same<XT, uint8_t>::value && p.tex_R >= 2) {
+        float ms = tw.base;
+#pragma unroll
+        for (int row = 0; row < 2; ++row) {
+            // taps l and l + 1, or one texel twice at an edge (at the right one
+            // the pair's second byte)
+            const int l = (int)B.t[2 * row], r = (int)B.t[2 * row + 1];
+            const int last = l == r && B.col != 0;
+            const uint32_t pair = *(const u16a1 *)((const char *)map + l - last);
+            const uint32_t e0 = last ? pair >> 8 : pair & 0xffu;
+            const uint32_t e1 = l == r ? e0 : pair >> 8;
+            ms += tw.w[2 * row] * (float)e0;
+            ms += tw.w[2 * row + 1] * (float)e1;
+        }
+        return ms;
+    }
+    return bilinear_elem<XT>(map, B, tw, 0);
+}
+
 // Eq. 2 as printed for SH degree DEG: S_a = sum_v Y_v(d) m[a nb + v] over
 // nb = (DEG + 1)^2 harmonics per axis, and the offset m_s(p_t) S.
 template <typename XT, int DEG>
@@ -258,16 +298,37 @@ __device__ __forceinline__ void vec3_offset(const RayParams &p, const Bilinear &
     const XT *tex = (const XT *)p.tex;
     const TapWeights<XT> tw(B, p.q_scale[0], p.q_offset[0]);
     float m[NCHUNK * EPV];
-    if (vec) {
+    if (vec && NCHUNK <= 4) {
+        // The two taps of a texture row are neighbours, often in one line: their
+        // chunks are loaded next to each other, row by row.
+        typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+        u4 raw[4][NCHUNK];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int q = 0; q < NCHUNK; ++q) {
+                raw[k][q] = *(const u4 *)(tex + B.t[k] + q * EPV);
+                load_order();
+            }
+#pragma unroll
+        for (int c = 0; c < NCHUNK * EPV; ++c) m[c] = tw.base;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int q = 0; q < NCHUNK; ++q) {
+                XT e[EPV];
+                __builtin_memcpy(e, &raw[k][q], 16);
+#pragma unroll
+                for (int i = 0; i < EPV; ++i) m[q * EPV + i] += tw.w[k] * (float)e[i];
+            }
+    } else if (vec) {
 #pragma unroll
         for (int q = 0; q < NCHUNK; ++q) bilinear_chunk<XT>(tex, B, tw, q * EPV, m + q * EPV);
     } else {
 #pragma unroll
         for (int c = 0; c < NCH; ++c) m[c] = bilinear_elem<XT>(tex, B, tw, c);
     }
-    const Bilinear Bs = bilinear_taps(p.tex_R, 1, u, v);
-    const float ms = bilinear_elem<XT>((const XT *)p.tex_scale, Bs,
-                                       TapWeights<XT>(Bs, p.q_scale[1], p.q_offset[1]), 0);
+    const float ms = scale_map<XT>(p, u, v);
     float S[3] = {0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int a = 0; a < 3; ++a)
@@ -732,15 +793,6 @@ constexpr bool kBlockPairs8 = F16 && TableEntry<F, F16>::kBytes == 8;
 // four, the masks cost more than the lines: view720p 489 -> 496 us, opaque
 // content 298 -> 304.
 enum GatherForm { kEntries = 0, kBlocksThenFar = 1, kBlocksWithFar = 2 };
-
-// Keeps the loads before it before those after it.  The two entries of an
-// x-neighbour pair mostly share a line, and the vector L1, which the waves of
-// a CU fill with 64 lines per gather, holds it for few gathers: with the
-// compiler free to mix the levels of a batch, the deployed grid's 1280x720
-// frame took 105 us, with the levels apart 97.8, and with every pair's loads
-// next to each other 91.6 (view720p 494, 491, 488.5; spread samples 854, 848,
-// 841).
-__device__ __forceinline__ void load_order() { asm volatile("" ::: "memory"); }
 
 template <int F, bool F16, bool DENSE, int FORM = kEntries>
 __device__ __forceinline__ void level_fetch(const void *table_l, const LevelSetup &s,

@@ -102,6 +102,26 @@ def test_ray_setup_blocks_across_rows_and_views(R, base, views, W, H, K):
     assert np.abs(x.cpu().numpy() - xd).max() <= 2e-5   # as test_ray_setup in test_gpu_parity
 
 
+@pytest.mark.parametrize("tex_R", [1, 2, 3, 64])
+@pytest.mark.parametrize("dtype,degree", [("u8", 2), ("f16", 2), ("f32", 1), ("f32", 3)])
+def test_vector_map_taps_at_the_edges(R, tex_R, dtype, degree):
+    """Eq. 2's vector form where two taps are one texel: coordinates on and
+    around every edge of the map, maps of one and two texels (the 8-bit scale
+    map reads its row's taps as one pair)."""
+    base = synth.TINY64_VEC3 if dtype == "f32" else synth.PAPER720P.replace(log2_T=8)
+    cfg = base.replace(name="edges", H=8, W=25, K=1, tex_R=tex_R, tex_dtype=dtype, sh_degree=degree)
+    say("map edges", tex_R, dtype, degree)
+    sc = synth.make_scene(cfg)
+    c = (np.arange(-1, tex_R + 2) + 0.5) / tex_R
+    c = np.concatenate([c, np.nextafter(c, 0), [0.0, 1.0, 0.5]]).astype(np.float32)
+    rng = np.random.default_rng(tex_R)
+    sc.g0[..., 1:3] = rng.choice(c, sc.g0.shape[:3] + (2,))
+    ds = mixrt.DeviceScene.from_scene(sc, "cuda:0")
+    x, _ = R.ray_setup(ds)
+    _, xd, _ = oracle.OracleScene(sc).pixel_samples(np.arange(cfg.rays))
+    assert np.abs(x.cpu().numpy() - xd).max() <= 2e-5   # as test_ray_setup in test_gpu_parity
+
+
 @pytest.mark.parametrize("W,H", [(16, 16), (64, 64), (161, 90), (240, 135)])
 @pytest.mark.parametrize("K,delta", [(4, 0.25), (8, 0.25), (8, 0.05), (8, 0.01), (32, 0.1)])
 def test_small_frames_render_the_same_in_every_round_size(W, H, K, delta):
