@@ -81,6 +81,8 @@ struct RasterLaunch {
     int32_t views, W, H;
     float4 *g0;
     float4 *g1;
+    int32_t per_wave;   // triangles per wave (1..64); with 1, `slices` waves share
+    int32_t slices;     // each triangle's pixels
 };
 
 hipError_t launch_rasterize(const RasterLaunch &L, hipStream_t stream);

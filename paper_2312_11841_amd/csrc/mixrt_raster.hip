@@ -6,15 +6,19 @@
 // (mixrt_raycast.hip).
 //
 //   clear:   every pixel's key = all ones (no hit);
-//   raster:  each wave takes 64 triangles of one view (strided over the
+//   raster:  each wave takes up to 64 triangles of one view (strided over the
 //            mesh, for balance between waves), clips them against a
 //            plane just in front of the camera, projects them and bounds
 //            their pixels (one pixel of margin); the (triangle, pixel) pairs
-//            of all 64 boxes, in box order, are cut into 64 equal runs, one
+//            of all boxes, in box order, are cut into 64 equal runs, one
 //            per lane, so large and small triangles balance within the wave;
 //            a lane finds its first box by binary search and then steps
 //            pixel by pixel, box by box, testing with the pixel's ray
-//            direction before normalisation (same order of hits);
+//            direction before normalisation (same order of hits).  The boxes
+//            with pixels stand first in LDS, so the next box is the next
+//            entry: skipping the triangles out of view one by one cost a
+//            chain of LDS reads at nearly every step (64x64 15.5 -> 14.1 us).
+//            Views of few triangles take a wave or more per triangle;
 //   resolve: per pixel, the winning triangle's hit is recomputed to write t,
 //            the barycentric uv and the face normal.
 // The winner of a pixel is the fp32 closest hit of its ray as the ray cast
@@ -137,6 +141,58 @@ __device__ __forceinline__ void pixel_box(const RasterLaunch &L, const CamK &c, 
     bh = (int)fy1 - y0 + 1;
 }
 
+// One (triangle, pixel) pair: the test with the pixel's ray direction before
+// normalisation (as in camera_ray), and the key's atomic minimum.
+__device__ __forceinline__ void test_pair(const RasterLaunch &L, const CamK &c, int64_t view_base,
+                                          const float4 &A, const float4 &E1, const float4 &E2,
+                                          int px, int py)
+{
+    const float cx = ((float)px + 0.5f - 0.5f * (float)L.W) * c.inv_f;
+    const float cy = -(((float)py + 0.5f - 0.5f * (float)L.H) * c.inv_f);
+    const float dx = c.R[0] * cx + c.R[1] * cy - c.R[2];
+    const float dy = c.R[3] * cx + c.R[4] * cy - c.R[5];
+    const float dz = c.R[6] * cx + c.R[7] * cy - c.R[8];
+    float st;
+    if (tri_hit_scaled(A, E1, E2, c.o[0], c.o[1], c.o[2], dx, dy, dz, dx * dx + dy * dy + dz * dz,
+                       st)) {
+        const uint64_t key = ((uint64_t)__float_as_uint(st) << 32) | (uint32_t)__float_as_int(A.w);
+        atomicMin((unsigned long long *)L.g0 + 2 * (view_base + (int64_t)py * L.W + px),
+                  (unsigned long long)key);
+    }
+}
+
+// Few triangles: a wave (or several) per triangle, its 64 lanes on
+// consecutive pixels of the box.
+__global__ __launch_bounds__(kBlock) void raster_large_kernel(const RasterLaunch L)
+{
+    const int view = blockIdx.y;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
+    const int64_t w = (int64_t)blockIdx.x * kWavesPerBlock + wv;
+    const int64_t tri = w / L.slices;
+    const int slice = (int)(w - tri * L.slices);
+    if (tri >= L.n_faces) return;
+    const CamK &c = L.cams[view];
+    const float4 A = L.tris[3 * tri], E1 = L.tris[3 * tri + 1], E2 = L.tris[3 * tri + 2];
+    int x0, y0, bw, bh;
+    pixel_box(L, c, L.near_z[view], A, E1, E2, x0, y0, bw, bh);
+    const int total = bw * bh;   // fewer than 2^26 pixels
+    const int step = kWave * L.slices;
+    int q = slice * kWave + lane;
+    if (q >= total) return;
+    int j = q / bw, i = q - j * bw;
+    const int dj = step / bw, di = step - dj * bw;
+    const int64_t view_base = (int64_t)view * L.H * L.W;
+    for (; q < total; q += step) {
+        test_pair(L, c, view_base, A, E1, E2, x0 + i, y0 + j);
+        i += di;
+        j += dj;
+        if (i >= bw) {
+            i -= bw;
+            ++j;
+        }
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void raster_kernel(const RasterLaunch L)
 {
     __shared__ Box s_box[kWavesPerBlock][kWave];
@@ -151,7 +207,7 @@ __global__ __launch_bounds__(kBlock) void raster_kernel(const RasterLaunch L)
     Box b;
     b.a = b.e1 = b.e2 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     b.x0 = b.y0 = b.bw = b.bh = 0;
-    if (tri < L.n_faces) {
+    if (lane < L.per_wave && tri < L.n_faces) {
         b.a = L.tris[3 * tri];
         b.e1 = L.tris[3 * tri + 1];
         b.e2 = L.tris[3 * tri + 2];
@@ -165,8 +221,17 @@ __global__ __launch_bounds__(kBlock) void raster_kernel(const RasterLaunch L)
         if (lane >= d) end += o;
     }
     b.end = end;
-    s_box[wv][lane] = b;
+    // the boxes with pixels first, in order, then the others (whose ends, the
+    // total, no run reaches): a lane's next box is the next entry
+    const uint64_t live = __ballot(b.bw * b.bh > 0);
+    const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(live >> 32),
+                                               __builtin_amdgcn_mbcnt_lo((uint32_t)live, 0u));
     const uint32_t total = __shfl(end, kWave - 1);
+    if (total == 0) return;   // (the whole wave)
+    if ((live >> lane) & 1)
+        s_box[wv][rank] = b;
+    else
+        s_box[wv][__popcll(live) + lane - rank].end = total;
     wave_lds_sync();
     // this lane's run of pairs [q0, q1)
     const uint32_t q0 = (uint32_t)(((uint64_t)total * lane) >> 6);
@@ -183,31 +248,13 @@ __global__ __launch_bounds__(kBlock) void raster_kernel(const RasterLaunch L)
     int i = (int)(local - (uint32_t)j * (uint32_t)bx->bw);
     float4 A = bx->a, E1 = bx->e1, E2 = bx->e2;
     int x0 = bx->x0, y0 = bx->y0, bw = bx->bw, bh = bx->bh;
-    uint64_t *vis = (uint64_t *)L.g0;
     const int64_t view_base = (int64_t)view * L.H * L.W;
     for (uint32_t q = q0; q < q1; ++q) {
-        const int px = x0 + i, py = y0 + j;
-        // the pixel's ray direction before normalisation (as in camera_ray)
-        const float cx = ((float)px + 0.5f - 0.5f * (float)L.W) * c.inv_f;
-        const float cy = -(((float)py + 0.5f - 0.5f * (float)L.H) * c.inv_f);
-        const float dx = c.R[0] * cx + c.R[1] * cy - c.R[2];
-        const float dy = c.R[3] * cx + c.R[4] * cy - c.R[5];
-        const float dz = c.R[6] * cx + c.R[7] * cy - c.R[8];
-        float st;
-        if (tri_hit_scaled(A, E1, E2, c.o[0], c.o[1], c.o[2], dx, dy, dz,
-                           dx * dx + dy * dy + dz * dz, st)) {
-            const uint64_t key = ((uint64_t)__float_as_uint(st) << 32) | (uint32_t)__float_as_int(A.w);
-            atomicMin((unsigned long long *)&vis[2 * (view_base + (int64_t)py * L.W + px)],
-                      (unsigned long long)key);
-        }
+        test_pair(L, c, view_base, A, E1, E2, x0 + i, y0 + j);
         if (++i == bw) {
             i = 0;
             if (++j == bh && q + 1 < q1) {
-                // next box with pixels (empty boxes hold no pair)
-                do {
-                    ++cur;
-                } while (s_box[wv][cur].bw * s_box[wv][cur].bh == 0);
-                bx = &s_box[wv][cur];
+                bx = &s_box[wv][++cur];
                 A = bx->a;
                 E1 = bx->e1;
                 E2 = bx->e2;
@@ -257,14 +304,37 @@ __global__ __launch_bounds__(kBlock) void resolve_kernel(const RasterLaunch L)
 
 }  // namespace
 
+// How the triangles are dealt to waves, by the pixels per triangle of a view
+// (the mean box grows with them; what a view shows is not known here).
+// From 6 on, a wave or more per triangle (raster_large_kernel), one for about
+// every 24 pixels: 499,712 triangles at 2560x1440 277 -> 208 us, 32,000 at
+// 1280x720 150 -> 36, 3,632 there 767 -> 36 and at 2560x1440 2986 -> 97; at
+// 4.15 pixels (1920x1080) it took 178 us against 155.
+// Below, fewer triangles per wave the larger they are, so that more waves share
+// the work and no wave draws many large ones: 8 from one pixel on (1.84 pixels
+// 83 -> 79 us; 125,000 triangles at 960x540 55 -> 47), 16 from 0.3, else 64
+// (499,712 at 64x64 16.5 us, 17.4 with 32, 32.6 with 8).
+static void raster_split(RasterLaunch &L)
+{
+    const double px = (double)L.W * L.H / (double)L.n_faces;
+    const int slices = (int)fmin(px / 24.0, 4096.0);
+    L.slices = slices > 1 ? slices : 1;
+    L.per_wave = px >= 6.0 ? 1 : px >= 1.0 ? 8 : px >= 0.3 ? 16 : 64;
+}
+
 hipError_t launch_rasterize(const RasterLaunch &L, hipStream_t stream)
 {
     const int64_t pixels = (int64_t)L.views * L.H * L.W;
     const int pix_blocks = (int)((pixels + kBlock - 1) / kBlock);
     hipLaunchKernelGGL(clear_kernel, dim3(pix_blocks), dim3(kBlock), 0, stream, (uint4 *)L.g0,
                        pixels);
-    const int tri_blocks = (int)(((int64_t)L.n_faces + kBlock - 1) / kBlock);
-    hipLaunchKernelGGL(raster_kernel, dim3(tri_blocks, L.views), dim3(kBlock), 0, stream, L);
+    RasterLaunch R = L;
+    raster_split(R);
+    const int64_t waves = R.per_wave > 1 ? ((int64_t)L.n_faces + R.per_wave - 1) / R.per_wave
+                                         : (int64_t)L.n_faces * R.slices;
+    const dim3 grid((unsigned)((waves + kWavesPerBlock - 1) / kWavesPerBlock), L.views);
+    hipLaunchKernelGGL(R.per_wave > 1 ? raster_kernel : raster_large_kernel, grid, dim3(kBlock), 0,
+                       stream, R);
     hipLaunchKernelGGL(resolve_kernel, dim3(pix_blocks), dim3(kBlock), 0, stream, L);
     return hipGetLastError();
 }

@@ -162,3 +162,48 @@ def test_samples_on_the_far_faces_of_the_cube(R, K):
         got = R.render(ds).cpu().numpy()
         ref = oracle.OracleScene(sc).render_pixels(np.arange(cfg.rays))
         assert np.abs(got - ref).max() <= 2e-3
+
+
+@pytest.mark.parametrize("W,H", [(8, 8), (33, 32), (61, 60), (148, 147), (149, 147), (400, 300)])
+@pytest.mark.parametrize("views", [1, 3])
+def test_rasterised_views_of_every_split(R, W, H, views):
+    """Pixels per triangle from 0.02 to 33: 64, 16 and 8 triangles per wave, one
+    wave per triangle and several; the ray cast finds the same triangle at all
+    but the pixels where two meet."""
+    mesh = synth.make_mesh(8, room_level=3, n_objects=6, object_level=2, n_boxes=4, box_div=3)
+    cams = synth.make_scene(synth.TINY64.replace(H=8, W=8, views=views, gbuf="room")).cams
+    # turned a little: views along the mesh's symmetry planes meet its edges
+    # pixel after pixel, where either triangle may win
+    a, b = 0.123, 0.071
+    turn = np.array([[np.cos(a), 0, np.sin(a)], [0, 1, 0], [-np.sin(a), 0, np.cos(a)]]) @ \
+        np.array([[1, 0, 0], [0, np.cos(b), -np.sin(b)], [0, np.sin(b), np.cos(b)]])
+    for v in range(views):
+        m = cams[v, :12].reshape(3, 4).astype(np.float64)
+        m[:, :3] = m[:, :3] @ turn
+        cams[v, :12] = m.reshape(-1)
+    say("raster", W, H, views, W * H / len(mesh.faces))
+    dm = mixrt.DeviceMesh(R, mesh)
+    a0, a1 = (t.cpu().numpy() for t in R.rasterize(dm, cams, W, H))
+    b0, b1 = (t.cpu().numpy() for t in R.raycast(dm, cams, W, H))
+    dm.close()
+    same = a1[..., 3].view(np.int32) == b1[..., 3].view(np.int32)
+    assert (~same).sum() <= max(2, 1e-3 * same.size)
+    # the winner's hit is solved by the same operations on the same ray
+    assert np.abs(a0[same] - b0[same]).max() <= 1e-5
+    assert np.array_equal(a1[same][:, :3], b1[same][:, :3])
+
+
+@pytest.mark.parametrize("W,H", [(1, 1), (64, 64), (640, 200)])
+def test_one_triangle_fills_the_view(R, W, H):
+    """One triangle over the whole image: its pixels go to many waves."""
+    mesh = synth.Mesh(positions=np.array([[-90, -90, -3], [90, -90, -3], [0, 120, -3]], np.float32),
+                      faces=np.array([[0, 1, 2]], np.int32), uv=np.zeros((3, 2), np.float32))
+    cam = np.zeros((1, 16), np.float32)
+    cam[0, [0, 5, 10]] = 1.0
+    cam[0, 12] = 60.0
+    dm = mixrt.DeviceMesh(R, mesh)
+    g0, g1 = (t.cpu().numpy() for t in R.rasterize(dm, cam, W, H))
+    c0, _ = (t.cpu().numpy() for t in R.raycast(dm, cam, W, H))
+    dm.close()
+    assert (g1[..., 3].view(np.int32) == 0).all()
+    assert np.abs(g0 - c0).max() <= 1e-5
