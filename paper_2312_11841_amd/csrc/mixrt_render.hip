@@ -738,10 +738,10 @@ static int render_block_from(const RenderLaunch &L)
 // block; elsewhere the lanes share more lines and the one change of the lane
 // mask is cheaper (the tile path on 2 MiB levels: 116 against 119 us at K = 1,
 // 443 against 447 at K = 5).
-static bool render_far_last(const RenderLaunch &L)
+static bool render_far_last(const RenderLaunch &L, int round)
 {
     const int64_t level_bytes = ((int64_t)L.gp.T_mask + 1) * 4;
-    return render_round(L) != 1 && level_bytes <= L.l2_bytes;
+    return round != 1 && level_bytes <= L.l2_bytes;
 }
 
 // Hashed levels per batch of gathers: 4 for entries of 8 or more bytes
@@ -805,12 +805,12 @@ hipError_t launch_render(const RenderLaunch &L0, hipStream_t stream)
     RenderLaunch L = L0;
     L.gp.block_from = render_block_from(L);
     L.gp.hash_batch = render_hash_batch(L);
-    L.gp.far_last = render_far_last(L);
+    const int chunk = render_round(L);
+    L.gp.far_last = render_far_last(L, chunk);
 #define X(a, b, c, d, e, f)                                                                    \
     if (MIXRT_RENDER_MATCH(a, b, c, d, e, f)) {                                                \
         int64_t blocks;                                                                        \
         int stripe;                                                                            \
-        const int chunk = render_round(L);                                                     \
         unsigned int *work = render_claims(L) ? L.work : nullptr;                              \
         render_shape(L, render_resident<a, b, c, d, e, f>(chunk > 0), blocks, stripe);         \
         if (chunk > 0)                                                                         \
