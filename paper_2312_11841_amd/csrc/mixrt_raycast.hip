@@ -76,23 +76,6 @@ __device__ __forceinline__ void test_tri(const Tri &T, uint32_t r, const Ray &ra
     }
 }
 
-// The walk, in units of cells: the ray is o + t d with o and d scaled by the
-// cell size (t is unchanged), a cell is its integer coordinates held as
-// floats, and tn[a] = (c + face[a]) inv[a] is the distance to its next face on
-// axis a (face holds -o and which of the two faces; inf where the ray does
-// not move on the axis).  Scaled coordinates err by about 1e-5 of a cell,
-// triangles are listed in cells padded by 1/500.
-struct Walk {
-    float o[3], d[3], inv[3], face[3], st[3];
-    float c[3], tn[3];
-};
-
-__device__ __forceinline__ void faces(Walk &w)
-{
-#pragma unroll
-    for (int a = 0; a < 3; ++a) w.tn[a] = (w.c[a] + w.face[a]) * w.inv[a];
-}
-
 // Move out of the empty cube c +- (leap - 1) (for leap = 1 the cell itself)
 // through its nearest face: that axis moves leap cells, the others go to the
 // cell holding the exit point, kept inside the cube, so never backwards.  One
@@ -118,7 +101,7 @@ __device__ __forceinline__ bool advance(const MeshGridK &g, int leap, Walk &w)
         w.c[a] = exit ? far[a] + w.st[a] : __builtin_amdgcn_fmed3f(at, w.c[a], far[a]);
         in = in && w.c[a] >= 0.0f && w.c[a] < (float)g.n[a];
     }
-    faces(w);
+    walk_faces(w);
     return in;
 }
 
@@ -132,26 +115,9 @@ __device__ __forceinline__ Hit cast(const MeshGridK &g, const Ray &r)
 {
     Hit h{kInf, 0.0f, 0.0f, INT32_MAX, 0u};
     const float o[3] = {r.ox, r.oy, r.oz}, d[3] = {r.dx, r.dy, r.dz};
-    float t0 = 0.0f, t1 = kInf;
+    float t_in;
     Walk w;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const float inv = 1.0f / d[a];
-        const float ta = (g.lo[a] - o[a]) * inv, tb = (g.hi[a] - o[a]) * inv;
-        t0 = fmaxf(t0, fminf(ta, tb));
-        t1 = fminf(t1, fmaxf(ta, tb));
-        w.o[a] = (o[a] - g.lo[a]) * g.inv_cell[a];
-        w.d[a] = d[a] * g.inv_cell[a];
-        const bool moves = d[a] > 0.0f || d[a] < 0.0f;
-        w.st[a] = moves ? copysignf(1.0f, d[a]) : 0.0f;
-        w.inv[a] = moves ? inv * g.cell[a] : 1.0f;
-        w.face[a] = moves ? (d[a] > 0.0f ? 1.0f : 0.0f) - w.o[a] : kInf;
-    }
-    if (!(t0 <= t1) || !(t0 < kInf)) return h;
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-        w.c[a] = fminf(fmaxf(floorf(w.o[a] + t0 * w.d[a]), 0.0f), (float)(g.n[a] - 1));
-    faces(w);
+    if (!walk_enter(g, o, d, w, t_in)) return h;
     // Every move goes at least one cell along the ray's direction on some
     // axis and never back on any, so the walk leaves the grid within
     // nx + ny + nz moves; the counter bounds it whatever the rounding.
@@ -178,7 +144,7 @@ __device__ __forceinline__ Hit cast(const MeshGridK &g, const Ray &r)
             test_tri(T, k, r, h);
             T = nT;
         }
-        if (h.t <= fminf(w.tn[0], fminf(w.tn[1], w.tn[2]))) break;
+        if (h.t <= t_in + fminf(w.tn[0], fminf(w.tn[1], w.tn[2]))) break;
         if (--steps <= 0 || !advance(g, 1, w)) break;
         rec = cell_rec(g, w);
     }
