@@ -13,14 +13,15 @@ namespace mixrt {
 // (22 MB written), now 17.3; the
 // 8-bit vector map's 921,600 samples take 7 us less.
 template <int TEX>
-__global__ __launch_bounds__(kBlock) void ray_setup_kernel(RayParams rp, float *__restrict__ out_x,
+__global__ __launch_bounds__(kBlock) void ray_setup_kernel(RayParams rp, uint32_t first_block,
+                                                           float *__restrict__ out_x,
                                                            int32_t *__restrict__ out_hit)
 {
     typedef typename TexOf<TEX>::type TK;
     __shared__ float s_x[3 * kBlock];
     const uint32_t t = threadIdx.x, K = (uint32_t)rp.K;
     const uint32_t R = kBlock / K;
-    const uint32_t ray0 = blockIdx.x * R;
+    const uint32_t ray0 = (first_block + blockIdx.x) * R;
     const uint32_t n = min(R, (uint32_t)rp.rays - ray0);   // rays of this block
     // t / K: exact for t < 2^8 and K <= 64
     const uint32_t inv = (65536u + K - 1u) / K;
@@ -398,18 +399,27 @@ hipError_t launch_ray_setup(const RayParams &rp, int tex, float *out_x, int32_t 
 {
     if (rp.rays == 0) return hipSuccess;
     const int R = kBlock / rp.K;   // rays per block (K is at most 64)
-    const dim3 grid((unsigned)(((int64_t)rp.rays + R - 1) / R));
+    // A launch holds fewer than 2^32 threads.  A block whose K does not divide it
+    // leaves lanes idle, so frames of fewer than 2^32 samples may need two.
+    constexpr int64_t kMost = (int64_t(1) << 24) - 1;
+    const int64_t blocks = ((int64_t)rp.rays + R - 1) / R;
+    for (int64_t first = 0; first < blocks; first += kMost) {
+        const dim3 grid((unsigned)(blocks - first < kMost ? blocks - first : kMost));
 #define T(ID)                                                                                  \
     case ID:                                                                                   \
-        hipLaunchKernelGGL(ray_setup_kernel<ID>, grid, dim3(kBlock), 0, stream, rp, out_x, out_hit); \
+        hipLaunchKernelGGL(ray_setup_kernel<ID>, grid, dim3(kBlock), 0, stream, rp,            \
+                           (uint32_t)first, out_x, out_hit);                                   \
         break;
-    switch (tex) {
-        T(kTexF32Ray) T(kTexF16Ray) T(kTexU8Ray) T(kTexF32Vec3D1) T(kTexF16Vec3D2) T(kTexU8Vec3D2)
-        T(kTexNone) T(kTexF32Vec3) T(kTexF16Vec3) T(kTexU8Vec3)
-    default: return hipErrorInvalidValue;
-    }
+        switch (tex) {
+            T(kTexF32Ray) T(kTexF16Ray) T(kTexU8Ray) T(kTexF32Vec3D1) T(kTexF16Vec3D2)
+            T(kTexU8Vec3D2) T(kTexNone) T(kTexF32Vec3) T(kTexF16Vec3) T(kTexU8Vec3)
+        default: return hipErrorInvalidValue;
+        }
 #undef T
-    return hipGetLastError();
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_hash_encode(const GridParams &gp, int F, bool tf16, const float *x, int64_t n,

@@ -102,6 +102,37 @@ def test_ray_setup_blocks_across_rows_and_views(R, base, views, W, H, K):
     assert np.abs(x.cpu().numpy() - xd).max() <= 2e-5   # as test_ray_setup in test_gpu_parity
 
 
+def test_ray_setup_of_more_threads_than_one_launch_holds(R):
+    """52 samples per ray leave 48 of a block's 256 lanes idle: 3.6e9 samples
+    take more than 2^32 threads.  The second view equals a call of its own
+    (which fits one launch) bit for bit."""
+    if torch.cuda.mem_get_info()[1] < 96 << 30:
+        pytest.skip("needs 70 GB of device memory")
+    W, H, K = 8700, 4000, 52
+    assert 2 * W * H * K < 1 << 32 <= 2 * W * H // (256 // K) * 256
+    base = synth.TINY64_DENSE.replace(name="long", views=2, W=8, H=8, K=K, delta=0.05, disp="none")
+    sc = synth.make_scene(base)
+    ds = mixrt.DeviceScene.from_scene(sc, "cuda:0")
+    g0 = torch.rand((2, H, W, 4), dtype=torch.float32, device="cuda:0")
+    g0[..., 0] += 0.5
+    say("ray_setup", W, H, K)
+
+    def setup(first):
+        ds.g0 = g0[first:]
+        ds.cams = mixrt.make_cameras(sc.cams[first:])
+        ds.gbuf = mixrt.GBuffer(2 - first, W, H, ds.g0.data_ptr(), 0)
+        ds.rays = (2 - first) * W * H
+        return R.ray_setup(ds)
+
+    both, _ = setup(0)
+    one, hit = setup(1)
+    assert bool((hit == 1).all())
+    assert torch.equal(both[W * H:], one)
+    assert float(one[-1].sum()) > 0.0
+    del both, one, g0
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("tex_R", [1, 2, 3, 64])
 @pytest.mark.parametrize("dtype,degree", [("u8", 2), ("f16", 2), ("f32", 1), ("f32", 3)])
 def test_vector_map_taps_at_the_edges(R, tex_R, dtype, degree):
