@@ -273,9 +273,7 @@ typedef struct {
     int32_t blocks;      /* persistent grid, blocks of 256 threads */
     int32_t tile_stripe; /* tile-order stripe width in tiles (the image's tile
                             columns for row-major order) */
-    int32_t chunk;       /* samples per ray per round (0: all K at once); with
-                            the library's choice, a frame with too few tiles
-                            for that takes more at once, up to all K */
+    int32_t chunk;       /* samples per ray per round (0: all K at once) */
     int32_t block_from;  /* first hash level whose x-neighbour corner pairs
                             are gathered as 16-byte blocks (L: none) */
     int32_t hash_batch;  /* hashed levels per batch of gathers (2 or 4) */

@@ -848,14 +848,14 @@ hipError_t phase_cycles_read(uint64_t *out, bool reset)
 hipError_t render_launch_shape(const RenderLaunch &L, int *blocks, int *stripe, int *chunk,
                                int *block_from, int *hash_batch, int *claims)
 {
+    *chunk = render_round(L);
     *block_from = render_block_from(L);
     *hash_batch = render_hash_batch(L);
     *claims = render_claims(L) ? 1 : 0;
 #define X(a, b, c, d, e, f)                                                                    \
     if (MIXRT_RENDER_MATCH(a, b, c, d, e, f)) {                                                \
         int64_t nb;                                                                            \
-        *chunk = render_chunk(L);                                                              \
-        render_shape(L, render_resident<a, b, c, d, e, f>(render_round(L) > 0), nb, *stripe); \
+        render_shape(L, render_resident<a, b, c, d, e, f>(*chunk > 0), nb, *stripe);           \
         *blocks = (int)nb;                                                                     \
         return hipSuccess;                                                                     \
     }

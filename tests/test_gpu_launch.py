@@ -251,13 +251,14 @@ BLOCK_CFGS = [
 def test_block_gathers_give_the_same_frame(cfg):
     """16-byte block gathers of x-neighbour corner pairs read the same two
     entries as single gathers: every choice of levels renders the same bits,
-    on the tile path and in rounds."""
+    on the tile path, in the library's rounds and in rounds of one (where the
+    entries of straddling voxels are loaded each with its block)."""
     say("block gathers", cfg.name)
     sc = synth.make_scene(cfg)
     ds = mixrt.DeviceScene.from_scene(sc, "cuda:0")
     ref = None
     seen = set()
-    for chunk in (-1, 0):
+    for chunk in (-1, 0, 1):
         for levels in (-1, 0, 1, 3, cfg.L):
             r = mixrt.Renderer(0, sync_check=True, early_stop_chunk=chunk, block_levels=levels)
             seen.add(r.launch_plan(ds)["block_from"])
@@ -289,6 +290,27 @@ def test_block_gathers_spot_check_against_the_oracle(cfg):
     assert np.abs(got[pix] - ref).max() <= 2e-3
 
 
+def _plan(cfg, W, H, views=1):
+    """The launch plan of a frame of W x H x views pixels.  (A plan reads no
+    device memory: the scene behind the descriptors is a small one.)"""
+    ds = mixrt.DeviceScene.from_scene(synth.make_scene(cfg.replace(H=16, W=64, views=1)), "cuda:0")
+    ds.gbuf = mixrt.GBuffer(views, W, H, ds.g0.data_ptr(), 0)
+    ds.cams = type(ds.cams)._type_.__mul__(views)(*([ds.cams[0]] * views))
+    r = mixrt.Renderer(0)
+    plan = r.launch_plan(ds)
+    r.close()
+    return plan
+
+
+def _frame_of(tiles, K):
+    """(W, H) of a frame of exactly that many tiles, one above the other: 64 / K
+    pixels each, four times as wide as high or more (K a power of two)."""
+    R, rows = 64 // K, 1
+    while rows * rows * 16 <= R:
+        rows *= 2
+    return R // rows, rows * tiles
+
+
 @pytest.mark.parametrize("cfg", [synth.VIEW720P, synth.VIEW720P_DENSE,
                                  synth.VIEW720P_DENSE.replace(name="d05", delta=0.05),
                                  synth.VIEW720P.replace(name="k2", K=2),
@@ -296,17 +318,33 @@ def test_block_gathers_spot_check_against_the_oracle(cfg):
                                  synth.BATCH8X1080P, synth.PAPER720P],
                          ids=lambda c: c.name)
 def test_default_round_size_follows_the_rule(cfg):
-    """The library's default samples per round (0 = the tile path): 4 when a
-    ray's samples share the voxels of half the levels and a level fits one
-    XCD's L2, 2 or 1 as they share fewer, the tile path for K < 4 or K not a
-    power of two and for coherent samples on levels larger than the L2."""
+    """The library's default samples per round (0 = the tile path) at the
+    workload's own size: 4 when a ray's samples share the voxels of half the
+    levels and a level fits one XCD's L2, 2 or 1 as they share fewer, the
+    tile path for K < 4 or K not a power of two and for coherent samples on
+    levels larger than the L2."""
     want = {"view720p": 4, "view720p_dense": 1, "d05": 2, "k2": 0, "k3": 0,
             "batch8x1080p": 0, "paper720p": 0}[cfg.name]
-    sc = synth.make_scene(cfg.replace(H=16, W=64, views=1))
-    ds = mixrt.DeviceScene.from_scene(sc, "cuda:0")
-    r = mixrt.Renderer(0)
-    assert r.launch_shape(ds, chunk=True)[2] == want
-    r.close()
+    assert _plan(cfg, cfg.W, cfg.H, cfg.views)["chunk"] == want
+
+
+@pytest.mark.parametrize("K,delta,first", [(8, 0.25, 1), (8, 0.05, 2), (8, 0.01, 4), (4, 0.25, 1),
+                                           (16, 0.25, 1)])
+def test_default_round_size_of_small_frames(K, delta, first):
+    """The plan names the round that is launched: doubled as often as it takes
+    for half of 3 waves per SIMD to get a run of K / C tiles, on both sides of
+    every step, up to the tile path."""
+    cfg = synth.VIEW720P_DENSE.replace(name="small_plan", K=K, delta=delta)
+    waves = 12 * torch.cuda.get_device_properties(0).multi_processor_count
+    C = first
+    while C < K:
+        enough = K * waves // (2 * C)              # tiles from which rounds of C stay
+        assert _plan(cfg, *_frame_of(enough, K))["chunk"] == C, (C, enough)
+        if C > first:
+            assert _plan(cfg, *_frame_of(2 * enough - 1, K))["chunk"] == C, (C, enough)
+        C *= 2
+    assert _plan(cfg, *_frame_of(enough - 1, K))["chunk"] == 0
+    assert _plan(cfg, *_frame_of(1, K))["chunk"] == 0
 
 
 @pytest.mark.parametrize("cfg", [synth.VIEW720P, synth.VIEW720P_DENSE,
