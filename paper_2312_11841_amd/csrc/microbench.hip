@@ -425,8 +425,11 @@ int mixrt_mb_gather_replay(const float *x, const int32_t *hit, int32_t views, in
     gp.L = L;
     gp.block_from = block_from < 0 ? 0 : block_from > L ? L : block_from;
     gp.hash_batch = hash_batch;
-    // (the render's rule, with the 4 MiB L2 of one XCD)
-    gp.far_last = chunk != 1 && log2_T <= 20;
+    int device = 0, l2_bytes = 0;
+    hipError_t e = hipGetDevice(&device);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&l2_bytes, hipDeviceAttributeL2CacheSize, device);
+    if (e != hipSuccess) return e;
+    gp.far_last = mixrt::far_entries_last(chunk, gp.log2_T, l2_bytes);
     const uint64_t T = 1ull << log2_T;
     for (int l = 0; l < L; ++l) {
         if (N[l] < 1 || N[l] > (1 << 20) || (l > 0 && N[l] < N[l - 1])) return hipErrorInvalidValue;

@@ -207,6 +207,19 @@ __host__ __device__ inline TilePos tile_at(const TileShape &t, int s)
     return p;
 }
 
+// Whether the x + 1 entries of straddling voxels are loaded after a level's
+// four blocks instead of each with its block (tables of 4-byte entries):
+// see level_fetch for both sides.  In rounds of one sample per ray and on
+// levels larger than one XCD's L2, whose lines are dear, each goes with its
+// block; elsewhere the lanes share more lines and the one change of the lane
+// mask is cheaper (the tile path on 2 MiB levels: 116 against 119 us at K = 1,
+// 443 against 447 at K = 5).  The render and the replay of its gathers both ask
+// here.  round: samples per ray per round, 0 for the tile path.
+inline bool far_entries_last(int round, uint32_t log2_T, int64_t l2_bytes)
+{
+    return round != 1 && (int64_t(4) << log2_T) <= l2_bytes;
+}
+
 __device__ __forceinline__ void wave_lds_sync()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");

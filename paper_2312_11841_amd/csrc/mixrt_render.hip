@@ -731,19 +731,6 @@ static int render_block_from(const RenderLaunch &L)
     return nl - finest > lo ? nl - finest : (lo < nl ? lo : nl);
 }
 
-// Whether the x + 1 entries of straddling voxels are loaded after a level's
-// four blocks instead of each with its block (tables of 4-byte entries):
-// see level_fetch for both sides.  In rounds of one sample per ray and on
-// levels larger than one XCD's L2, whose lines are dear, each goes with its
-// block; elsewhere the lanes share more lines and the one change of the lane
-// mask is cheaper (the tile path on 2 MiB levels: 116 against 119 us at K = 1,
-// 443 against 447 at K = 5).
-static bool render_far_last(const RenderLaunch &L, int round)
-{
-    const int64_t level_bytes = ((int64_t)L.gp.T_mask + 1) * 4;
-    return round != 1 && level_bytes <= L.l2_bytes;
-}
-
 // Hashed levels per batch of gathers: 4 for entries of 8 or more bytes
 // (F = 4 fp16 and up) when one batch then covers every hashed level of a
 // query (at most 4), so a wave waits for its table once per tile instead of
@@ -806,7 +793,7 @@ hipError_t launch_render(const RenderLaunch &L0, hipStream_t stream)
     L.gp.block_from = render_block_from(L);
     L.gp.hash_batch = render_hash_batch(L);
     const int chunk = render_round(L);
-    L.gp.far_last = render_far_last(L, chunk);
+    L.gp.far_last = far_entries_last(chunk, L.gp.log2_T, L.l2_bytes);
 #define X(a, b, c, d, e, f)                                                                    \
     if (MIXRT_RENDER_MATCH(a, b, c, d, e, f)) {                                                \
         int64_t blocks;                                                                        \
