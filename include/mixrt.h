@@ -413,7 +413,7 @@ int mixrt_raycast(mixrt_ctx *ctx, const mixrt_mesh *mesh, int32_t views, int32_t
  * obtains it: by rasterising the mesh (Fig. 2 step 1) with compute kernels
  * into a visibility buffer of (t, triangle) keys kept by atomic minimum.
  * Faster than mixrt_raycast for whole frames.  The keys live in out_g0
- * until the last of the call's three launches overwrites them, so no
+ * until the last of the call's launches overwrites them, so no
  * device memory is allocated.  Fewer than 2^26 pixels per view
  * (MIXRT_EUNSUPPORTED beyond); other arguments as for mixrt_raycast. */
 int mixrt_rasterize(mixrt_ctx *ctx, const mixrt_mesh *mesh, int32_t views, int32_t W, int32_t H,

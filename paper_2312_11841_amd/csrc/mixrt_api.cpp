@@ -606,6 +606,7 @@ int mixrt_rasterize(mixrt_ctx *ctx, const mixrt_mesh *mesh, int32_t views, int32
     L.views = views;
     L.W = W;
     L.H = H;
+    L.cus = ctx->cus;
     L.g0 = (float4 *)out_g0;
     L.g1 = (float4 *)out_g1;
     return finish_launch(ctx, mixrt::launch_rasterize(L, ctx->stream), "rasterize");

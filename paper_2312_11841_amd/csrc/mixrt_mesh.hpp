@@ -132,10 +132,11 @@ struct RasterLaunch {
     CamK cams[MIXRT_MAX_VIEWS];
     float near_z[MIXRT_MAX_VIEWS];
     int32_t views, W, H;
+    int32_t cus;
     float4 *g0;
     float4 *g1;
-    int32_t per_wave;   // triangles per wave (1..64); with 1, `slices` waves share
-    int32_t slices;     // each triangle's pixels
+    int32_t per_wave;   // triangles per wave (1..64)
+    int32_t list_from;  // boxes of more pixels go to the list (0: none do)
 };
 
 hipError_t launch_rasterize(const RasterLaunch &L, hipStream_t stream);

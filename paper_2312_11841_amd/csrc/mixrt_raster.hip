@@ -7,24 +7,29 @@
 //
 //   clear:   every pixel's key = all ones (no hit);
 //   raster:  each wave takes up to 64 triangles of one view (strided over the
-//            mesh, for balance between waves), clips them against a
-//            plane just in front of the camera, projects them and bounds
-//            their pixels (one pixel of margin); the (triangle, pixel) pairs
-//            of all boxes, in box order, are cut into 64 equal runs, one
-//            per lane, so large and small triangles balance within the wave;
-//            a lane finds its first box by binary search and then steps
-//            pixel by pixel, box by box, testing with the pixel's ray
+//            mesh, for balance between waves), one per lane, clips them against
+//            a plane just in front of the camera, projects them and bounds
+//            their pixels (one pixel of margin).  Large boxes go to a list.  Of
+//            the others the (triangle, pixel) pairs, in box order, are cut into
+//            64 equal runs, one per lane, so large and small triangles balance
+//            within the wave; a lane finds its first box by binary search and
+//            then steps pixel by pixel, box by box, testing with the pixel's ray
 //            direction before normalisation (same order of hits).  The boxes
 //            with pixels stand first in LDS, so the next box is the next
 //            entry: skipping the triangles out of view one by one cost a
 //            chain of LDS reads at nearly every step (64x64 15.5 -> 14.1 us).
-//            Views of few triangles take a wave or more per triangle;
+//            Boxes of kWideMean pixels and more on average are drawn one after
+//            another instead, 64 consecutive pixels at a time;
+//   list:    the listed boxes, one wave per 1024 pixels of them;
 //   resolve: per pixel, the winning triangle's hit is recomputed to write t,
 //            the barycentric uv and the face normal.
 // The winner of a pixel is the fp32 closest hit of its ray as the ray cast
 // finds it, except where two triangles' hits lie within rounding of each
-// other.  The keys live in the first 8 bytes of each 16-byte G-buffer record: the
-// three launches need no memory beyond the caller's output.
+// other.  The keys live in the first 8 bytes of each 16-byte G-buffer record and
+// the list in the second: the launches need no memory beyond the caller's output.
+//
+// What bounds it: the pairs' VALU work in view, the set-up of every triangle and
+// the launches out of it.
 #include "mixrt_common.hpp"
 #include "mixrt_mesh.hpp"
 
@@ -161,28 +166,59 @@ __device__ __forceinline__ void test_pair(const RasterLaunch &L, const CamK &c, 
     }
 }
 
-// Few triangles: a wave (or several) per triangle, its 64 lanes on
-// consecutive pixels of the box.
-__global__ __launch_bounds__(kBlock) void raster_large_kernel(const RasterLaunch L)
+// The list of large boxes of a view, in the second 8 bytes of the view's G-buffer
+// records (which the clear leaves zero and the keys do not touch): kLists parts,
+// so that no counter takes every wave's atomic, each with its counter in record
+// 16 p (a line of its own) and its entries, (triangle + 1, slice), from record
+// kListHead + p part on.  An entry of zero was reserved and not used.
+constexpr int kLists = kWave;           // the list kernel's lanes read a counter each
+constexpr int kListHead = 16 * kLists;
+constexpr int kSlicePixels = 1024, kMaxSlices = 256;
+// (499,712 triangles from outside at 1280x720: 60 us, 79 with 40, 129 with 32)
+constexpr uint32_t kWideMean = 64;
+
+__device__ __forceinline__ unsigned long long *list_word(const RasterLaunch &L, int64_t view_base,
+                                                         int64_t record)
 {
-    const int view = blockIdx.y;
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
-    const int64_t w = (int64_t)blockIdx.x * kWavesPerBlock + wv;
-    const int64_t tri = w / L.slices;
-    const int slice = (int)(w - tri * L.slices);
-    if (tri >= L.n_faces) return;
-    const CamK &c = L.cams[view];
-    const float4 A = L.tris[3 * tri], E1 = L.tris[3 * tri + 1], E2 = L.tris[3 * tri + 2];
-    int x0, y0, bw, bh;
-    pixel_box(L, c, L.near_z[view], A, E1, E2, x0, y0, bw, bh);
-    const int total = bw * bh;   // fewer than 2^26 pixels
-    const int step = kWave * L.slices;
+    return (unsigned long long *)L.g0 + 2 * (view_base + record) + 1;
+}
+
+__device__ __forceinline__ uint32_t list_part(const RasterLaunch &L)
+{
+    return ((uint32_t)L.W * (uint32_t)L.H - kListHead) / kLists;
+}
+
+// Waves that share a listed box: one per kSlicePixels, at most kMaxSlices.
+__device__ __forceinline__ uint32_t box_slices(uint32_t area)
+{
+    const uint32_t n = (area + kSlicePixels - 1) / kSlicePixels;
+    return n < kMaxSlices ? n : kMaxSlices;
+}
+
+// Sum of v over lanes 0..lane.
+__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v, int lane)
+{
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const uint32_t o = __shfl_up(v, d);
+        if (lane >= d) v += o;
+    }
+    return v;
+}
+
+// Every n-th 64 pixels of one box, from the `slice`-th on, by a wave whose lanes
+// take consecutive pixels (the box and its triangle are uniform).
+__device__ __forceinline__ void draw_box(const RasterLaunch &L, const CamK &c, int64_t view_base,
+                                         const float4 &A, const float4 &E1, const float4 &E2,
+                                         int x0, int y0, int bw, int bh, int slice, int n, int lane)
+{
+    const int area = bw * bh;   // fewer than 2^26 pixels
     int q = slice * kWave + lane;
-    if (q >= total) return;
+    if (q >= area) return;
+    const int step = kWave * n;
     int j = q / bw, i = q - j * bw;
     const int dj = step / bw, di = step - dj * bw;
-    const int64_t view_base = (int64_t)view * L.H * L.W;
-    for (; q < total; q += step) {
+    for (; q < area; q += step) {
         test_pair(L, c, view_base, A, E1, E2, x0 + i, y0 + j);
         i += di;
         j += dj;
@@ -193,16 +229,62 @@ __global__ __launch_bounds__(kBlock) void raster_large_kernel(const RasterLaunch
     }
 }
 
+// The listed boxes, in slices: a wave draws every n-th 64 pixels of its entry's
+// box.  The grid does not know how many entries there are; its waves stride over
+// them.
+__global__ __launch_bounds__(kBlock) void raster_list_kernel(const RasterLaunch L)
+{
+    const int view = blockIdx.y;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
+    const int64_t view_base = (int64_t)view * L.H * L.W;
+    const uint32_t part = list_part(L);
+    // (64 lines: read once per block)
+    __shared__ uint32_t s_count[kLists];
+    if (wv == 0) s_count[lane] = (uint32_t)*list_word(L, view_base, 16 * lane);
+    __syncthreads();
+    const uint32_t count = s_count[lane];
+    const uint32_t ends = wave_inclusive_sum(count < part ? count : part, lane);
+    const uint32_t total = __builtin_amdgcn_readlane(ends, kWave - 1);
+    const CamK &c = L.cams[view];
+    for (uint32_t e = blockIdx.x * kWavesPerBlock + wv; e < total; e += gridDim.x * kWavesPerBlock) {
+        const int p = __popcll(__ballot(ends <= e));
+        const uint32_t first = p ? __builtin_amdgcn_readlane(ends, p - 1) : 0u;
+        const uint64_t entry =
+            *list_word(L, view_base, kListHead + (int64_t)p * part + (e - first));
+        const uint32_t tri1 = __builtin_amdgcn_readfirstlane((uint32_t)entry);
+        if (tri1 == 0) continue;
+        const int64_t tri = (int64_t)tri1 - 1;
+        const float4 A = L.tris[3 * tri], E1 = L.tris[3 * tri + 1], E2 = L.tris[3 * tri + 2];
+        int x0, y0, bw, bh;
+        pixel_box(L, c, L.near_z[view], A, E1, E2, x0, y0, bw, bh);
+        draw_box(L, c, view_base, A, E1, E2, x0, y0, bw, bh, (int)(entry >> 32),
+                 (int)box_slices(bw * bh), lane);
+    }
+}
+
+__device__ __forceinline__ float lane_value(float v, int lane)
+{
+    return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), lane));
+}
+
+__device__ __forceinline__ float4 lane_value(const float4 &v, int lane)
+{
+    return make_float4(lane_value(v.x, lane), lane_value(v.y, lane), lane_value(v.z, lane),
+                       lane_value(v.w, lane));
+}
+
 __global__ __launch_bounds__(kBlock) void raster_kernel(const RasterLaunch L)
 {
     __shared__ Box s_box[kWavesPerBlock][kWave];
     const int view = blockIdx.y;
-    const int wv = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
     // Triangles are dealt to waves with a stride of the wave count, so that
     // the large boxes of a nearby object (consecutive triangles) spread over
     // many waves instead of piling into a few.
     const int64_t n_waves = (int64_t)gridDim.x * kWavesPerBlock;
-    const int64_t tri = (int64_t)lane * n_waves + (int64_t)blockIdx.x * kWavesPerBlock + wv;
+    const int64_t wave = (int64_t)blockIdx.x * kWavesPerBlock + wv;
+    const int64_t tri = (int64_t)lane * n_waves + wave;
+    const int64_t view_base = (int64_t)view * L.H * L.W;
     const CamK &c = L.cams[view];
     Box b;
     b.a = b.e1 = b.e2 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -213,22 +295,55 @@ __global__ __launch_bounds__(kBlock) void raster_kernel(const RasterLaunch L)
         b.e2 = L.tris[3 * tri + 2];
         pixel_box(L, c, L.near_z[view], b.a, b.e1, b.e2, b.x0, b.y0, b.bw, b.bh);
     }
-    // inclusive prefix sum of the box areas over the wave
-    uint32_t end = (uint32_t)b.bw * (uint32_t)b.bh;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const uint32_t o = __shfl_up(end, d);
-        if (lane >= d) end += o;
+    uint32_t area = (uint32_t)b.bw * (uint32_t)b.bh;
+    if (L.list_from > 0) {
+        // large boxes go to the list, unless this wave's do not all fit in its
+        // part (a part that is full is left alone, so that its counter cannot
+        // wrap)
+        const uint32_t n = area > (uint32_t)L.list_from ? box_slices(area) : 0u;
+        if (__ballot(n > 0)) {
+            const uint32_t end = wave_inclusive_sum(n, lane);
+            const uint32_t all = __builtin_amdgcn_readlane(end, kWave - 1);
+            const uint32_t part = list_part(L);
+            const int p = (int)(wave & (kLists - 1));
+            unsigned int *const ctr = (unsigned int *)list_word(L, view_base, 16 * p);
+            uint32_t base = part;
+            if (lane == 0 && __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < part)
+                base = atomicAdd(ctr, all);
+            base = __builtin_amdgcn_readfirstlane(base);
+            if (base + all <= part) {
+                unsigned long long *const word =
+                    list_word(L, view_base, kListHead + (int64_t)p * part + base + end - n);
+                for (uint32_t k = 0; k < n; ++k)
+                    __hip_atomic_store(word + 2 * k,
+                                       (unsigned long long)k << 32 | (uint32_t)(tri + 1),
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (n > 0) area = 0;
+            }
+        }
     }
+    // inclusive prefix sum of the areas of the boxes drawn here
+    const uint32_t end = wave_inclusive_sum(area, lane);
     b.end = end;
     // the boxes with pixels first, in order, then the others (whose ends, the
     // total, no run reaches): a lane's next box is the next entry
-    const uint64_t live = __ballot(b.bw * b.bh > 0);
+    const uint64_t live = __ballot(area > 0);
     const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(live >> 32),
                                                __builtin_amdgcn_mbcnt_lo((uint32_t)live, 0u));
-    const uint32_t total = __shfl(end, kWave - 1);
+    const uint32_t total = __builtin_amdgcn_readlane(end, kWave - 1);
     if (total == 0) return;   // (the whole wave)
-    if ((live >> lane) & 1)
+    if (total >= kWideMean * (uint32_t)__popcll(live)) {
+        // one box after another, 64 consecutive pixels at a time
+        for (uint64_t m = live; m; m &= m - 1) {
+            const int l = __builtin_ctzll(m);
+            draw_box(L, c, view_base, lane_value(b.a, l), lane_value(b.e1, l), lane_value(b.e2, l),
+                     __builtin_amdgcn_readlane(b.x0, l), __builtin_amdgcn_readlane(b.y0, l),
+                     __builtin_amdgcn_readlane(b.bw, l), __builtin_amdgcn_readlane(b.bh, l), 0, 1,
+                     lane);
+        }
+        return;
+    }
+    if (area > 0)
         s_box[wv][rank] = b;
     else
         s_box[wv][__popcll(live) + lane - rank].end = total;
@@ -248,7 +363,6 @@ __global__ __launch_bounds__(kBlock) void raster_kernel(const RasterLaunch L)
     int i = (int)(local - (uint32_t)j * (uint32_t)bx->bw);
     float4 A = bx->a, E1 = bx->e1, E2 = bx->e2;
     int x0 = bx->x0, y0 = bx->y0, bw = bx->bw, bh = bx->bh;
-    const int64_t view_base = (int64_t)view * L.H * L.W;
     for (uint32_t q = q0; q < q1; ++q) {
         test_pair(L, c, view_base, A, E1, E2, x0 + i, y0 + j);
         if (++i == bw) {
@@ -304,22 +418,35 @@ __global__ __launch_bounds__(kBlock) void resolve_kernel(const RasterLaunch L)
 
 }  // namespace
 
-// How the triangles are dealt to waves, by the pixels per triangle of a view
-// (the mean box grows with them; what a view shows is not known here).
-// From 6 on, a wave or more per triangle (raster_large_kernel), one for about
-// every 24 pixels: 499,712 triangles at 2560x1440 277 -> 208 us, 32,000 at
-// 1280x720 150 -> 36, 3,632 there 767 -> 36 and at 2560x1440 2986 -> 97; at
-// 4.15 pixels (1920x1080) it took 178 us against 155.
-// Below, fewer triangles per wave the larger they are, so that more waves share
-// the work and no wave draws many large ones: 8 from one pixel on (1.84 pixels
-// 83 -> 79 us; 125,000 triangles at 960x540 55 -> 47), 16 from 0.3, else 64
-// (499,712 at 64x64 16.5 us, 17.4 with 32, 32.6 with 8).
+// How a frame's triangles are dealt.  What a view shows is not known here, so the
+// deal costs no more than a set-up per triangle, 64 to a wave, where the mesh
+// is out of view, and the waves find out what is large:
+//  - as few triangles per wave as leave one wave per slot of the card (8 per
+//    SIMD): more waves would only queue;
+//  - boxes go to the list from the size on at which they would keep their wave
+//    busy after the others: 128 pixels where a wave holds 16 triangles or more
+//    (499,712 triangles at 1920x1080 115 us, 149 from 256 on; seen from outside
+//    at 1280x720 60 us, 71 from 64 on, where most waves pay for an atomic), 768
+//    where it holds few (32,000 from outside at 1280x720 33 us from 512 on, 31
+//    from 1024; 3,632 inside 33.9 and 35.0);
+//  - no list in views of fewer than 2^17 pixels, where its launch costs more
+//    than the boxes it would spread.
+// Measured, us, 64 triangles in every wave and no list / a wave or more per
+// triangle from 6 pixels per triangle on / this; room seen from inside, from
+// 120 units away, and behind the camera:
+//   499,712 at 1280x720    98 /  88 /  81    32 /  51 /  35    18 /  24 /  23
+//   499,712 at 2560x1440  330 / 220 / 166    52 / 226 /  55    36 / 117 /  39
+//   125,000 at 1280x720    96 /  66 /  57    20 /  60 /  24    14 /  32 /  19
+//     3,632 at 1280x720   896 /  32 /  34    24 /  23 /  19    12 /  18 /  18
+// and with one wall close by (499,712 at 2560x1440) 497 / 397 / 96.
 static void raster_split(RasterLaunch &L)
 {
-    const double px = (double)L.W * L.H / (double)L.n_faces;
-    const int slices = (int)fmin(px / 24.0, 4096.0);
-    L.slices = slices > 1 ? slices : 1;
-    L.per_wave = px >= 6.0 ? 1 : px >= 1.0 ? 8 : px >= 0.3 ? 16 : 64;
+    constexpr int64_t kListPixels = 1 << 17;
+    static_assert(kListPixels >= kListHead + kLists, "the list needs a record per part");
+    L.per_wave = 1;
+    while (L.per_wave < 64 && (int64_t)L.n_faces * L.views > (int64_t)L.per_wave * 32 * L.cus)
+        L.per_wave *= 2;
+    L.list_from = (int64_t)L.W * L.H < kListPixels ? 0 : L.per_wave >= 16 ? 128 : 768;
 }
 
 hipError_t launch_rasterize(const RasterLaunch &L, hipStream_t stream)
@@ -330,11 +457,13 @@ hipError_t launch_rasterize(const RasterLaunch &L, hipStream_t stream)
                        pixels);
     RasterLaunch R = L;
     raster_split(R);
-    const int64_t waves = R.per_wave > 1 ? ((int64_t)L.n_faces + R.per_wave - 1) / R.per_wave
-                                         : (int64_t)L.n_faces * R.slices;
-    const dim3 grid((unsigned)((waves + kWavesPerBlock - 1) / kWavesPerBlock), L.views);
-    hipLaunchKernelGGL(R.per_wave > 1 ? raster_kernel : raster_large_kernel, grid, dim3(kBlock), 0,
-                       stream, R);
+    const int64_t waves = ((int64_t)L.n_faces + R.per_wave - 1) / R.per_wave;
+    const unsigned blocks = (unsigned)((waves + kWavesPerBlock - 1) / kWavesPerBlock);
+    hipLaunchKernelGGL(raster_kernel, dim3(blocks, L.views), dim3(kBlock), 0, stream, R);
+    if (R.list_from > 0)
+        // one wave per slot of the card
+        hipLaunchKernelGGL(raster_list_kernel, dim3((8 * L.cus + L.views - 1) / L.views, L.views),
+                           dim3(kBlock), 0, stream, R);
     hipLaunchKernelGGL(resolve_kernel, dim3(pix_blocks), dim3(kBlock), 0, stream, L);
     return hipGetLastError();
 }

@@ -195,24 +195,22 @@ def test_samples_on_the_far_faces_of_the_cube(R, K):
         assert np.abs(got - ref).max() <= 2e-3
 
 
-@pytest.mark.parametrize("W,H", [(8, 8), (33, 32), (61, 60), (148, 147), (149, 147), (400, 300)])
-@pytest.mark.parametrize("views", [1, 3])
-def test_rasterised_views_of_every_split(R, W, H, views):
-    """Pixels per triangle from 0.02 to 33: 64, 16 and 8 triangles per wave, one
-    wave per triangle and several; the ray cast finds the same triangle at all
-    but the pixels where two meet."""
-    mesh = synth.make_mesh(8, room_level=3, n_objects=6, object_level=2, n_boxes=4, box_div=3)
-    cams = synth.make_scene(synth.TINY64.replace(H=8, W=8, views=views, gbuf="room")).cams
-    # turned a little: views along the mesh's symmetry planes meet its edges
-    # pixel after pixel, where either triangle may win
+def _turned(cams):
+    """Cameras turned a little: views along the mesh's symmetry planes meet its
+    edges pixel after pixel, where either triangle may win."""
     a, b = 0.123, 0.071
     turn = np.array([[np.cos(a), 0, np.sin(a)], [0, 1, 0], [-np.sin(a), 0, np.cos(a)]]) @ \
         np.array([[1, 0, 0], [0, np.cos(b), -np.sin(b)], [0, np.sin(b), np.cos(b)]])
-    for v in range(views):
-        m = cams[v, :12].reshape(3, 4).astype(np.float64)
+    for c in cams:
+        m = c[:12].reshape(3, 4).astype(np.float64)
         m[:, :3] = m[:, :3] @ turn
-        cams[v, :12] = m.reshape(-1)
-    say("raster", W, H, views, W * H / len(mesh.faces))
+        c[:12] = m.reshape(-1)
+    return cams
+
+
+def _same_hits(R, mesh, cams, W, H):
+    """The rasteriser's G-buffer against the ray cast's: the same triangle at all
+    but the pixels where two meet, and there its hit."""
     dm = mixrt.DeviceMesh(R, mesh)
     a0, a1 = (t.cpu().numpy() for t in R.rasterize(dm, cams, W, H))
     b0, b1 = (t.cpu().numpy() for t in R.raycast(dm, cams, W, H))
@@ -222,6 +220,79 @@ def test_rasterised_views_of_every_split(R, W, H, views):
     # the winner's hit is solved by the same operations on the same ray
     assert np.abs(a0[same] - b0[same]).max() <= 1e-5
     assert np.array_equal(a1[same][:, :3], b1[same][:, :3])
+    return a0
+
+
+MESHES = {   # faces -> make_mesh arguments
+    3632: dict(room_level=3, n_objects=6, object_level=2, n_boxes=4, box_div=3),
+    32000: dict(room_level=5, n_objects=8, object_level=3, n_boxes=4, box_div=5),
+    125000: dict(room_level=6, n_objects=24, object_level=3, n_boxes=16, box_div=8),
+}
+
+
+@pytest.mark.parametrize("W,H", [(9, 8), (61, 60), (400, 300)])
+@pytest.mark.parametrize("faces,views,per_wave", [(3632, 1, 1), (3632, 4, 2), (32000, 1, 4),
+                                                  (32000, 2, 8), (32000, 4, 16), (32000, 8, 32),
+                                                  (32000, 16, 64), (125000, 1, 16)])
+def test_rasterised_views_of_every_split(R, faces, views, per_wave, W, H):
+    """1 to 64 triangles per wave (as few as leave a wave per slot of the card),
+    in boxes from one pixel to thousands."""
+    mesh = synth.make_mesh(8, **MESHES[faces])
+    slots = 32 * torch.cuda.get_device_properties(0).multi_processor_count
+    n = len(mesh.faces) * views
+    assert n <= per_wave * slots and (per_wave == 1 or n > per_wave // 2 * slots)
+    cams = _turned(synth.make_scene(synth.TINY64.replace(H=8, W=8, views=views, gbuf="room")).cams)
+    say("raster", faces, W, H, views, per_wave)
+    _same_hits(R, mesh, cams, W, H)
+
+
+@pytest.mark.parametrize("W,H,views", [(362, 362, 1), (512, 256, 1), (517, 255, 3), (1280, 720, 2)])
+@pytest.mark.parametrize("faces", [3632, 125000])
+@pytest.mark.parametrize("where", ["inside", "outside", "behind"])
+def test_rasterised_views_with_and_without_a_list(R, where, faces, W, H, views):
+    """Views of 2^17 pixels and more keep large boxes in a list, among the keys in
+    the G-buffer: on both sides of that size, in every view of a call, from
+    inside the room, from outside and with the mesh behind the camera."""
+    mesh = synth.make_mesh(8, **MESHES[faces])
+    cams = _turned(synth.make_scene(synth.TINY64.replace(H=8, W=8, views=views, gbuf="room")).cams)
+    for c in cams:
+        back = c[:12].reshape(3, 4)[:, 2].astype(np.float64)      # the camera looks along -back
+        c[[3, 7, 11]] += {"inside": 0.0, "outside": 14.0, "behind": -40.0}[where] * back
+    say("raster list", where, faces, W, H, views)
+    g0 = _same_hits(R, mesh, cams, W, H)
+    assert (g0[..., 0] > 0).any() == (where != "behind")
+
+
+def _sheets(n, reach):
+    """n parallel triangles over the view of a camera at the origin, the farthest
+    first, at depths 1 to 3 (60 degrees see 0.58 of the depth on either side)."""
+    z = np.linspace(3.0, 1.0, n)[:, None]
+    xy = np.array([[-reach, -reach], [3 * reach, -reach], [-reach, 3 * reach]])
+    pos = np.concatenate([np.broadcast_to(xy, (n, 3, 2)),
+                          np.broadcast_to(-z[..., None], (n, 3, 1))], 2).astype(np.float32)
+    return synth.Mesh(positions=pos.reshape(-1, 3),
+                      faces=np.arange(3 * n, dtype=np.int32).reshape(-1, 3),
+                      uv=np.zeros((3 * n, 2), np.float32))
+
+
+@pytest.mark.parametrize("n", [1, 65, 900, 3000])
+def test_more_large_boxes_than_the_list_holds(R, n):
+    """Triangles that fill a view of 2^17 pixels take 128 entries each, and the
+    list's 64 parts hold 2,032: from 1,016 triangles on some do not fit, and
+    their waves draw them.  The nearest one wins everywhere."""
+    W, H = 512, 256
+    cam = np.zeros((1, 16), np.float32)
+    cam[0, [0, 5, 10]] = 1.0
+    cam[0, 12] = 60.0
+    dm = mixrt.DeviceMesh(R, _sheets(n, 20.0), grid_res=(1, 1, 1))
+    say("raster sheets", n)
+    g0, g1 = (t.cpu().numpy() for t in R.rasterize(dm, cam, W, H))
+    dm.close()
+    assert (g1[..., 3].view(np.int32) == n - 1).all()
+    z = 1.0 if n > 1 else 3.0
+    v = np.hypot(*np.meshgrid(np.arange(W) + 0.5 - W / 2, np.arange(H) + 0.5 - H / 2))
+    t = z * np.sqrt(1.0 + (v * np.tan(np.radians(30)) / (H / 2)) ** 2)
+    assert np.abs(g0[0, ..., 0] - t).max() <= 1e-4   # edges of 80 at depths of 3, in fp32
 
 
 @pytest.mark.parametrize("W,H", [(1, 1), (64, 64), (640, 200)])
