@@ -10,18 +10,20 @@ namespace mixrt {
 // than the block's rays, from scalar registers; lanes divide only small
 // numbers.  Positions leave through LDS in whole lines.  A 64-bit division and
 // two 32-bit ones a sample were most of the 19.8 us that 1.84 M samples took
-// (22 MB written), now 17.3; the
-// 8-bit vector map's 921,600 samples take 7 us less.
+// (22 MB written), now 17.3; the 8-bit vector map's 921,600 samples take 7 us
+// less.
+constexpr uint32_t kSetupBlocks = (1u << 24) - 1u;   // blocks of one row of the grid
+
 template <int TEX>
-__global__ __launch_bounds__(kBlock) void ray_setup_kernel(RayParams rp, uint32_t first_block,
-                                                           float *__restrict__ out_x,
+__global__ __launch_bounds__(kBlock) void ray_setup_kernel(RayParams rp, float *__restrict__ out_x,
                                                            int32_t *__restrict__ out_hit)
 {
     typedef typename TexOf<TEX>::type TK;
     __shared__ float s_x[3 * kBlock];
     const uint32_t t = threadIdx.x, K = (uint32_t)rp.K;
     const uint32_t R = kBlock / K;
-    const uint32_t ray0 = (first_block + blockIdx.x) * R;
+    const uint32_t ray0 = (blockIdx.y * kSetupBlocks + blockIdx.x) * R;
+    if (ray0 >= (uint32_t)rp.rays) return;   // (the last row's blocks past the end)
     const uint32_t n = min(R, (uint32_t)rp.rays - ray0);   // rays of this block
     // t / K: exact for t < 2^8 and K <= 64
     const uint32_t inv = (65536u + K - 1u) / K;
@@ -399,27 +401,23 @@ hipError_t launch_ray_setup(const RayParams &rp, int tex, float *out_x, int32_t 
 {
     if (rp.rays == 0) return hipSuccess;
     const int R = kBlock / rp.K;   // rays per block (K is at most 64)
-    // A launch holds fewer than 2^32 threads.  A block whose K does not divide it
-    // leaves lanes idle, so frames of fewer than 2^32 samples may need two.
-    constexpr int64_t kMost = (int64_t(1) << 24) - 1;
+    // A launch holds fewer than 2^32 threads in x.  A block whose K does not
+    // divide it leaves lanes idle, so frames of fewer than 2^32 samples may
+    // need a second row of blocks.
     const int64_t blocks = ((int64_t)rp.rays + R - 1) / R;
-    for (int64_t first = 0; first < blocks; first += kMost) {
-        const dim3 grid((unsigned)(blocks - first < kMost ? blocks - first : kMost));
+    const dim3 grid((unsigned)(blocks < kSetupBlocks ? blocks : kSetupBlocks),
+                    (unsigned)((blocks + kSetupBlocks - 1) / kSetupBlocks));
 #define T(ID)                                                                                  \
     case ID:                                                                                   \
-        hipLaunchKernelGGL(ray_setup_kernel<ID>, grid, dim3(kBlock), 0, stream, rp,            \
-                           (uint32_t)first, out_x, out_hit);                                   \
+        hipLaunchKernelGGL(ray_setup_kernel<ID>, grid, dim3(kBlock), 0, stream, rp, out_x, out_hit); \
         break;
-        switch (tex) {
-            T(kTexF32Ray) T(kTexF16Ray) T(kTexU8Ray) T(kTexF32Vec3D1) T(kTexF16Vec3D2)
-            T(kTexU8Vec3D2) T(kTexNone) T(kTexF32Vec3) T(kTexF16Vec3) T(kTexU8Vec3)
-        default: return hipErrorInvalidValue;
-        }
-#undef T
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    switch (tex) {
+        T(kTexF32Ray) T(kTexF16Ray) T(kTexU8Ray) T(kTexF32Vec3D1) T(kTexF16Vec3D2) T(kTexU8Vec3D2)
+        T(kTexNone) T(kTexF32Vec3) T(kTexF16Vec3) T(kTexU8Vec3)
+    default: return hipErrorInvalidValue;
     }
-    return hipSuccess;
+#undef T
+    return hipGetLastError();
 }
 
 hipError_t launch_hash_encode(const GridParams &gp, int F, bool tf16, const float *x, int64_t n,
