@@ -5,13 +5,12 @@
 
 namespace mixrt {
 
-// A block takes kBlock / K whole rays, so that its first pixel comes from
-// scalar divisions and its camera, when it lies in one view of rows no shorter
-// than the block's rays, from scalar registers; lanes divide only small
-// numbers.  Positions leave through LDS in whole lines.  A 64-bit division and
-// two 32-bit ones a sample were most of the 19.8 us that 1.84 M samples took
-// (22 MB written), now 17.3; the 8-bit vector map's 921,600 samples take 7 us
-// less.
+// A block takes kBlock / K whole rays, so that lanes divide only small numbers to
+// find their sample.  Bound by VALU issue.  Collected in LDS and stored in whole
+// lines, with the camera of a block of one view in scalar registers, it took
+// longer (1280x720 at K = 8, the along-ray fp16 map 46.9 against 42.6 us, the
+// fp16 vector map of run-time degree 1 82.1 against 73.8), but for the fp16 map
+// of degree 2 (88.8 against 97.0; at K = 1 36.0 against 33.0).
 constexpr uint32_t kSetupBlocks = (1u << 24) - 1u;   // blocks of one row of the grid
 
 template <int TEX>
@@ -19,38 +18,21 @@ __global__ __launch_bounds__(kBlock) void ray_setup_kernel(RayParams rp, float *
                                                            int32_t *__restrict__ out_hit)
 {
     typedef typename TexOf<TEX>::type TK;
-    __shared__ float s_x[3 * kBlock];
     const uint32_t t = threadIdx.x, K = (uint32_t)rp.K;
     const uint32_t R = kBlock / K;
-    const uint32_t ray0 = (blockIdx.y * kSetupBlocks + blockIdx.x) * R;
-    if (ray0 >= (uint32_t)rp.rays) return;   // (the last row's blocks past the end)
-    const uint32_t n = min(R, (uint32_t)rp.rays - ray0);   // rays of this block
     // t / K: exact for t < 2^8 and K <= 64
     const uint32_t inv = (65536u + K - 1u) / K;
     const uint32_t r = (t * inv) >> 16, k = t - r * K;
-    const uint32_t hw = (uint32_t)rp.H * (uint32_t)rp.W;
-    const uint32_t view = ray0 / hw, rem = ray0 - view * hw;
-    const uint32_t j0 = rem / (uint32_t)rp.W, i0 = rem - j0 * (uint32_t)rp.W;
-    if (r < n) {
-        const uint32_t ray = ray0 + r;
-        Ray ry;
-        if (rem + n <= hw && R <= (uint32_t)rp.W) {
-            const bool wrap = i0 + r >= (uint32_t)rp.W;
-            ry = camera_ray(rp.cams[view], rp.W, rp.H, wrap ? i0 + r - (uint32_t)rp.W : i0 + r,
-                            wrap ? j0 + 1u : j0);
-        } else {
-            ry = pixel_ray(rp, (int32_t)ray);
-        }
-        float x0, x1, x2;
-        const bool hit = sample_position<TK>(rp, ry, rp.g0[ray], (int)k, x0, x1, x2);
-        s_x[3 * t + 0] = x0;
-        s_x[3 * t + 1] = x1;
-        s_x[3 * t + 2] = x2;
-        if (out_hit && k == 0) out_hit[ray] = hit ? 1 : 0;
-    }
-    __syncthreads();
-    float *const o = out_x + (int64_t)ray0 * K * 3;
-    for (uint32_t e = t; e < 3u * n * K; e += kBlock) o[e] = s_x[e];
+    const uint32_t ray = (blockIdx.y * kSetupBlocks + blockIdx.x) * R + r;
+    if (r >= R || ray >= (uint32_t)rp.rays) return;
+    const Ray ry = pixel_ray(rp, (int32_t)ray);
+    float x0, x1, x2;
+    const bool hit = sample_position<TK>(rp, ry, rp.g0[ray], (int)k, x0, x1, x2);
+    float *const o = out_x + ((int64_t)ray * K + k) * 3;
+    o[0] = x0;
+    o[1] = x1;
+    o[2] = x2;
+    if (out_hit && k == 0) out_hit[ray] = hit ? 1 : 0;
 }
 
 template <int F, bool TF16>
