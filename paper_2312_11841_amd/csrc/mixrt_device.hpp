@@ -162,6 +162,17 @@ struct TexKind {
     static constexpr int mode = MODE;
     static constexpr int degree = DEG;
     static constexpr int nb = (DEG + 1) * (DEG + 1);
+    static constexpr int ahead = 4;
+};
+
+// vec3_offset holds the taps of maps of up to `ahead` 16-byte chunks per texel at
+// once.  With FEW only of two: kernels of the 8-bit map of run-time degree that
+// would lose a wave per SIMD to degree 3's three chunks (the ray setup 4 waves
+// to 3, 1280x720 at K = 8 and degree 1 89 us against 75; rounds with 4-byte
+// features and the 32-wide MLP 3 waves to 2, 331 us against 261).
+template <typename TK, bool FEW>
+struct TapsAhead : TK {
+    static constexpr int ahead = FEW ? 2 : TK::ahead;
 };
 
 __device__ __forceinline__ float tex_elem(float e, float, float) { return e; }
@@ -287,7 +298,7 @@ __device__ __forceinline__ float scale_map(const RayParams &p, float u, float v)
 
 // Eq. 2 as printed for SH degree DEG: S_a = sum_v Y_v(d) m[a nb + v] over
 // nb = (DEG + 1)^2 harmonics per axis, and the offset m_s(p_t) S.
-template <typename XT, int DEG>
+template <typename XT, int DEG, int AHEAD>
 __device__ __forceinline__ void vec3_offset(const RayParams &p, const Bilinear &B, float u,
                                             float v, const float *Y, bool vec, float &ox,
                                             float &oy, float &oz)
@@ -298,7 +309,7 @@ __device__ __forceinline__ void vec3_offset(const RayParams &p, const Bilinear &
     const XT *tex = (const XT *)p.tex;
     const TapWeights<XT> tw(B, p.q_scale[0], p.q_offset[0]);
     float m[NCHUNK * EPV];
-    if (vec && NCHUNK <= 4) {
+    if (vec && NCHUNK <= AHEAD) {
         // The two taps of a texture row are neighbours, often in one line: their
         // chunks are loaded next to each other, row by row.
         typedef uint32_t u4 __attribute__((ext_vector_type(4)));
@@ -381,13 +392,13 @@ __device__ __forceinline__ void displacement(const RayParams &p, float u, float 
         oy = s * dy;
         oz = s * dz;
     } else if (TK::degree >= 0) {
-        vec3_offset<XT, (TK::degree >= 0 ? TK::degree : 0)>(p, B, u, v, Y, vec, ox, oy, oz);
+        vec3_offset<XT, (TK::degree >= 0 ? TK::degree : 0), TK::ahead>(p, B, u, v, Y, vec, ox, oy, oz);
     } else {
         switch (p.tex_degree) {
-        case 0: vec3_offset<XT, 0>(p, B, u, v, Y, vec, ox, oy, oz); break;
-        case 1: vec3_offset<XT, 1>(p, B, u, v, Y, vec, ox, oy, oz); break;
-        case 2: vec3_offset<XT, 2>(p, B, u, v, Y, vec, ox, oy, oz); break;
-        default: vec3_offset<XT, 3>(p, B, u, v, Y, vec, ox, oy, oz); break;
+        case 0: vec3_offset<XT, 0, TK::ahead>(p, B, u, v, Y, vec, ox, oy, oz); break;
+        case 1: vec3_offset<XT, 1, TK::ahead>(p, B, u, v, Y, vec, ox, oy, oz); break;
+        case 2: vec3_offset<XT, 2, TK::ahead>(p, B, u, v, Y, vec, ox, oy, oz); break;
+        default: vec3_offset<XT, 3, TK::ahead>(p, B, u, v, Y, vec, ox, oy, oz); break;
         }
     }
 }

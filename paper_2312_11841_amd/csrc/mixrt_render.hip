@@ -328,7 +328,7 @@ __global__ __launch_bounds__(kBlock) MIXRT_LIGHT_WAVES(NHID, HID) void render_qu
 #ifdef MIXRT_SPLIT_NO_DISP
     typedef TexKind<float, kDispNone> TK;
 #else
-    typedef typename TexOf<TEX>::type TK;
+    typedef TapsAhead<typename TexOf<TEX>::type, TEX == kTexU8Vec3 && F == 2> TK;
 #endif
     constexpr int LD = IN + 8;  // padded row of MLP inputs (halves), 16-byte multiple
     __shared__ __attribute__((aligned(16))) _Float16 s_rows[kWavesPerBlock][kWave * LD];

@@ -17,7 +17,7 @@ template <int TEX>
 __global__ __launch_bounds__(kBlock) void ray_setup_kernel(RayParams rp, float *__restrict__ out_x,
                                                            int32_t *__restrict__ out_hit)
 {
-    typedef typename TexOf<TEX>::type TK;
+    typedef TapsAhead<typename TexOf<TEX>::type, TEX == kTexU8Vec3> TK;
     const uint32_t t = threadIdx.x, K = (uint32_t)rp.K;
     const uint32_t R = kBlock / K;
     // t / K: exact for t < 2^8 and K <= 64

@@ -97,31 +97,41 @@ def test_kernels_use_no_scratch(source):
     assert {k: v for k, v in sizes.items() if v} == {}
 
 
-# The render kernels of the 1280x720 view and the 8-view batch (fp16 grid
-# of 2 features, along-ray map, MLP 48-64-64-4) and of the paper's deployed
-# grid, with the waves per SIMD their registers allow: 512 VGPRs per lane
-# and SIMD, allocated in granules of 8.
-HOT_KERNELS = {
-    "_ZN5mixrt19render_queue_kernelILi1ELi2ELb1ELi48ELi64ELi2EEE": 3,
-    "_ZN5mixrt13render_kernelILi1ELi2ELb1ELi48ELi64ELi2EEE": 3,
-    "_ZN5mixrt13render_kernelILi5ELi4ELb1ELi32ELi64ELi2EEE": 2,
-}
+# Kernels whose registers must leave a number of waves per SIMD (512 VGPRs per
+# lane and SIMD, allocated in granules of 8): the render kernels of the 1280x720
+# view and the 8-view batch (fp16 grid of 2 features, along-ray map, MLP
+# 48-64-64-4) and of the paper's deployed grid, the rounds of the 8-bit map of
+# run-time degree, the ray setups of the vector maps, the ray cast and the
+# rasteriser.
+HOT_KERNELS = [
+    ("mixrt_render", "_ZN5mixrt19render_queue_kernelILi1ELi2ELb1ELi48ELi64ELi2EEE", 3),
+    ("mixrt_render", "_ZN5mixrt13render_kernelILi1ELi2ELb1ELi48ELi64ELi2EEE", 3),
+    ("mixrt_render", "_ZN5mixrt13render_kernelILi5ELi4ELb1ELi32ELi64ELi2EEE", 2),
+    ("mixrt_render", "_ZN5mixrt13render_kernelILi9ELi2ELb0ELi16ELi32ELi1EEE", 3),
+    ("mixrt_render", "_ZN5mixrt19render_queue_kernelILi9ELi2ELb0ELi16ELi32ELi1EEE", 3),
+    ("mixrt_stages", "_ZN5mixrt16ray_setup_kernelILi4EEE", 4),
+    ("mixrt_stages", "_ZN5mixrt16ray_setup_kernelILi5EEE", 5),
+    ("mixrt_stages", "_ZN5mixrt16ray_setup_kernelILi8EEE", 4),
+    ("mixrt_stages", "_ZN5mixrt16ray_setup_kernelILi9EEE", 4),
+    ("mixrt_raycast", "_ZN5mixrt12_GLOBAL__N_114raycast_kernelE", 7),
+    ("mixrt_raster", "_ZN5mixrt12_GLOBAL__N_113raster_kernelE", 8),
+    ("mixrt_raster", "_ZN5mixrt12_GLOBAL__N_118raster_list_kernelE", 8),
+]
 
 
-def test_hot_kernels_keep_their_occupancy():
-    """The measured workloads' kernels keep the waves per SIMD their launch
-    rules and timings assume (a few more registers in these kernels have
-    cost 20% by dropping a wave)."""
+@pytest.mark.parametrize("source,prefix,waves", HOT_KERNELS, ids=[k[1][8:48] for k in HOT_KERNELS])
+def test_hot_kernels_keep_their_occupancy(source, prefix, waves):
+    """These kernels keep the waves per SIMD their launch rules and timings
+    assume (a few more registers have cost 20% by dropping a wave)."""
     from paper_2312_11841_amd import build
-    obj = os.path.join(build.OBJ_DIR, "mixrt_render.o")
+    obj = os.path.join(build.OBJ_DIR, source + ".o")
     if not os.path.exists(obj):
         pytest.skip("library objects not built")
     vgprs = _kernel_metadata(obj, "vgpr_count")
-    for prefix, waves in HOT_KERNELS.items():
-        found = [v for k, v in vgprs.items() if k.startswith(prefix)]
-        assert len(found) == 1, prefix
-        granule = (found[0] + 7) // 8 * 8
-        assert 512 // granule >= waves, (prefix, found[0])
+    found = [v for k, v in vgprs.items() if k.startswith(prefix.rstrip("E"))]
+    assert len(found) == 1, prefix
+    granule = (found[0] + 7) // 8 * 8
+    assert 512 // granule >= waves, (prefix, found[0])
 
 
 @pytest.mark.parametrize("variant", ["timer", "split_nodisp", "split_nohash", "split_nomlp"])
