@@ -72,8 +72,8 @@ __global__ __launch_bounds__(kBlock) void hash_encode_kernel(GridParams gp, cons
 }
 
 // The features alone, which is what a program that keeps them asks for.  A
-// wave takes 64 queries, two levels' gathers in flight, and collects up to 32
-// features of each in LDS; they leave in rows of 16-byte stores past the
+// wave takes 64 queries, one or two levels' gathers in flight, and collects up to
+// 32 features of each in LDS; they leave in rows of 16-byte stores past the
 // caches (written once, and the table's lines stay).  Written from the lanes
 // as they come, one 4-byte store per feature touches 64 lines and most lines
 // come back to memory in pieces: 473 us for 1.84 M queries of 16 levels
@@ -126,15 +126,20 @@ __global__ __launch_bounds__(kBlock) void hash_features_kernel(GridParams gp,
     float *const buf = s_f[wv];
     const int L = gp.L, LF = L * F;
     constexpr int kLevels = kFeatCols / F;
+    // Levels' gathers in flight: two of 4-byte entries (1.84 M scattered queries of
+    // 16 levels 1023 us, 1084 with one), one of larger ones, whose queries of small
+    // tables they kept waiting (8 levels of 2^14 fp32 pairs 236 us, 252 with two;
+    // 8 levels of 2^17 fp32 quads 79 and 89; Tab. 3's 14,400 queries 16.4 and 17.6).
+    constexpr int G = F == 2 && TF16 ? 2 : 1;
     for (int l0 = 0; l0 < L; l0 += kLevels) {
         const int l1 = l0 + kLevels < L ? l0 + kLevels : L;
         const int ld = gp.n_dense < l1 ? gp.n_dense : l1;
         const int lb = gp.block_from < l1 ? gp.block_from : l1;
         float *const row = buf + lane * kFeatRow - l0 * F;
         int l = l0;
-        for (; l + 2 <= ld; l += 2) features_of<F, TF16, 2, true, kEntries>(gp, l, x0, x1, x2, row + l * F);
+        for (; l + G <= ld; l += G) features_of<F, TF16, G, true, kEntries>(gp, l, x0, x1, x2, row + l * F);
         for (; l < ld; ++l) features_of<F, TF16, 1, true, kEntries>(gp, l, x0, x1, x2, row + l * F);
-        for (; l + 2 <= lb; l += 2) features_of<F, TF16, 2, false, kEntries>(gp, l, x0, x1, x2, row + l * F);
+        for (; l + G <= lb; l += G) features_of<F, TF16, G, false, kEntries>(gp, l, x0, x1, x2, row + l * F);
         for (; l < lb; ++l) features_of<F, TF16, 1, false, kEntries>(gp, l, x0, x1, x2, row + l * F);
         if constexpr (kBlockPairs<F, TF16> || kBlockPairs8<F, TF16>)
             for (; l < l1; ++l)
