@@ -298,17 +298,18 @@ __global__ __launch_bounds__(kBlock) void sum_head_kernel(const _Float16 *__rest
     out4[s] = mlp_activate(f4{acc[0], acc[1], acc[2], acc[3]});
 }
 
-// One sample per ray: the loads are whole lines as they are (700,000 rays with
-// the stage's MLP 23.9 us, 24.6 through LDS; with two samples 43.2 against 41.8).
-__global__ __launch_bounds__(kBlock) void composite_one_kernel(const float4 *__restrict__ srgb,
-                                                               int64_t rays, int, float delta,
-                                                               float t_term, float bg0, float bg1,
-                                                               float bg2, float4 *__restrict__ out)
+// One lane per ray, each loading its ray's samples: see composite_by_lane for
+// where.
+__global__ __launch_bounds__(kBlock) void composite_lane_kernel(const float4 *__restrict__ srgb,
+                                                                int64_t rays, int K, float delta,
+                                                                float t_term, float bg0, float bg1,
+                                                                float bg2, float4 *__restrict__ out)
 {
     const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (r >= rays) return;
     Composite cp;
-    cp.add(srgb[r], delta, t_term);
+    for (int k = 0; k < K; ++k)
+        if (!cp.add(srgb[r * K + k], delta, t_term)) break;
     out[r] = cp.finish(bg0, bg1, bg2);
 }
 
@@ -482,13 +483,23 @@ hipError_t launch_mlp(int in, int hid, int nhid, int hid_w, const _Float16 *weig
     return hipErrorInvalidValue;
 }
 
+// Whether each lane loads its own ray's samples.  Up to 4 samples are half a line,
+// which the L1 keeps until the lane's next ones (921,600 rays, us by lane / through
+// LDS, from the last level cache: K = 2 6.8 / 10.8, 3 11.4 / 13.9, 4 16.3 / 17.1, 5
+// 30.1 / 20.0; from memory 9.8 / 11.3, 13.3 / 14.7, 17.9 / 17.9, 31.8 / 20.8).  With
+// fewer than three waves per CU the L1 keeps every ray's lines, and the lane's
+// chain of loads is shorter than the chunks' (K = 64: 14,400 rays 10.3 / 12.7, 32,768
+// 11.4 / 13.4, 65,536 15.7 / 15.1; K = 32: 6.2 / 7.6, 6.5 / 8.0, 7.0 / 8.4).
+static bool composite_by_lane(int64_t rays, int K) { return K <= 4 || rays < 3 * 256 * kWave; }
+
 hipError_t launch_composite(const float4 *srgb, int64_t rays, int K, float delta, float t_term,
                             const float *bg, float4 *out, hipStream_t stream)
 {
     if (rays == 0) return hipSuccess;
     const dim3 grid((unsigned)((rays + kBlock - 1) / kBlock));
-    hipLaunchKernelGGL(K == 1 ? composite_one_kernel : composite_kernel, grid, dim3(kBlock), 0,
-                       stream, srgb, rays, K, delta, t_term, bg[0], bg[1], bg[2], out);
+    hipLaunchKernelGGL(composite_by_lane(rays, K) ? composite_lane_kernel : composite_kernel, grid,
+                       dim3(kBlock), 0, stream, srgb, rays, K, delta, t_term, bg[0], bg[1], bg[2],
+                       out);
     return hipGetLastError();
 }
 

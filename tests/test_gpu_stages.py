@@ -67,11 +67,12 @@ def test_features_alone_equal_the_full_encoding(R, grid, n):
     assert got[0] == 7.0 and (got[-2:] == 7.0).all()   # nothing around it
 
 
-@pytest.mark.parametrize("rays", [1, 63, 64, 65, 257])
-@pytest.mark.parametrize("K", [1, 2, 7, 8, 9, 16, 64])
+@pytest.mark.parametrize("rays", [1, 63, 64, 65, 257, 49151, 49152, 49153, 49215])
+@pytest.mark.parametrize("K", [1, 2, 4, 5, 7, 8, 9, 16, 64])
 def test_composite_tails(R, K, rays):
-    """Chunks of 8 samples over 64 rays: every remainder of both, rays that
-    stop early and rays that never do (the bar of the other composite test)."""
+    """One lane per ray (up to 4 samples, or fewer than 49,152 rays), and chunks
+    of 8 samples over 64 rays: every remainder of both, rays that stop early
+    and rays that never do (the bar of the other composite test)."""
     say("composite", K, rays)
     rng = np.random.default_rng(K * 1000 + rays)
     s = rng.random((rays, K, 4), dtype=np.float32)
