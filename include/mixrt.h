@@ -114,7 +114,8 @@ typedef struct {
                             features only; speed only, never a result): > 0
                             that many (hashed levels only), < 0 none, 0 the
                             library's choice (2 features: the three finest,
-                            up to seven at K < 4 as the pixels lie apart, five
+                            up to seven at K < 4 as its cells are finer than
+                            a few far pixels, five
                             in rounds of one sample per ray (seven at K >= 8),
                             both only in frames with a tile for every wave;
                             four when a level's table exceeds one XCD's L2

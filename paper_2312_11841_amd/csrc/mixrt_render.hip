@@ -675,12 +675,17 @@ static int render_round(const RenderLaunch &L)
 // 4-byte entries: blocks pay on levels whose lanes touch lines of their own
 // (coarser ones hand neighbouring lanes the same lines, where a 4-byte gather
 // is cheaper), so among the hashed levels finer than a ray's sample spacing:
-//  - one to three samples per ray, whose lanes are neighbouring pixels: the
-//    levels whose cells are finer than the pixels' spacing at a distance of 8,
-//    3 to 7 of them.  Against always 3, 1280x720 at K = 1 / 2 / 3 went from
-//    118 / 171 / 243 us to 103 / 160 / 232, 640x360 at K = 1 from 59.6 to 56.0,
-//    1920x1080 from 187 to 171, 2560x1440 from 281 to 257, and a 4096x4096 view
-//    keeps 3 (7 there: 1.06 ms as with 3, and at K = 2 2.03 against 1.93).
+//  - one to three samples per ray, whose lanes are neighbouring pixels: 3 to 7,
+//    the levels whose cells are at most 4 pixels wide at K = 1 and 2 at K = 2 and
+//    3, whose lanes also share a ray's lines.  The width is that of pixels on a
+//    surface facing the camera far away, 1 / (2 f) of the cube, which the
+//    contraction lets no distance exceed: what stands where is not known here.
+//    us with 3 / this many, with the view's depths, a quarter and four times
+//    them: K = 1 1280x720 120 / 109, 114 / 103, 127 / 116, 2560x1440 293 / 267,
+//    316 / 281, 286 / 260, 4096x2160 610 / 592, 684 / 661, 578 / 563; K = 2
+//    1280x720 181 / 171, 190 / 180, 156 / 148; K = 3 1280x720 253 / 246, 295 /
+//    278, 201 / 201, 2560x1440 779 / 774, 954 / 932, 653 / 666 (as many as at K =
+//    1: 774, 895, 693).
 //    Frames with fewer tiles than the card holds waves keep 3: nothing hides
 //    the blocks' one level per batch there (320x180: 30.5 us with 3, 32.1 with
 //    7);
@@ -713,12 +718,12 @@ static int render_block_from(const RenderLaunch &L)
         finest = L.rp.K >= 8 ? 8 : 4;
     } else if (L.rp.K < 4) {
         if (fills) {
-            // a pixel at distance 8, in grid units inside the unit ball
-            float spacing = 8.0f;
-            for (int v = 0; v < L.rp.views; ++v) spacing = fminf(spacing, 2.0f * L.rp.cams[v].inv_f);
+            float inv_f = L.rp.cams[0].inv_f;
+            for (int v = 1; v < L.rp.views; ++v) inv_f = fminf(inv_f, L.rp.cams[v].inv_f);
+            const float cell = (L.rp.K == 1 ? 2.0f : 1.0f) * inv_f;
             int finer = 0;
             for (int l = 0; l < nl; ++l)
-                if ((float)L.gp.N[l] * spacing >= 1.0f) ++finer;
+                if ((float)L.gp.N[l] * cell >= 1.0f) ++finer;
             finest = finer < 3 ? 3 : finer > 7 ? 7 : finer;
         }
     } else if (render_chunk(L) == 1) {

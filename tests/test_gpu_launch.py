@@ -347,32 +347,49 @@ def test_default_round_size_of_small_frames(K, delta, first):
     assert _plan(cfg, *_frame_of(1, K))["chunk"] == 0
 
 
-@pytest.mark.parametrize("cfg", [synth.VIEW720P, synth.VIEW720P_DENSE,
-                                 synth.VIEW720P.replace(name="k1", K=1),
-                                 synth.VIEW720P.replace(name="fine_spacing", delta=1e-4),
-                                 synth.BATCH8X1080P, synth.BATCH8X1080P.replace(name="batch_k4", K=4),
-                                 synth.PAPER720P, synth.DEPLOYED720P, synth.TABLE3[0],
-                                 _table3("tab3_L8_T5"),
-                                 _table3("tab3_L16_T17").replace(name="tab3_L16")],
-                         ids=lambda c: c.name)
-def test_default_gather_plan_follows_the_rule(cfg):
-    """4-byte entries: block gathers on the three finest levels (five in
-    rounds of one sample per ray; when a level's table exceeds one XCD's L2:
-    four, and eight at K >= 8) among hashed levels finer than the sample
-    spacing.  8-byte (fp16 F = 4)
-    entries: on every hashed level when there are 8 or more of them in tables
-    of 2^10 or more entries.  Batches of 4 hashed levels only for entries of
-    8+ bytes when that covers every hashed level."""
-    want = {"view720p": (13, 2), "view720p_dense": (11, 2), "k1": (13, 2),
-            "fine_spacing": (16, 2), "batch8x1080p": (8, 2), "batch_k4": (12, 2),
-            "paper720p": (4, 4), "deployed720p": (4, 4), "tab3_L8_T17_mlp": (0, 2),
-            "tab3_L8_T5": (8, 2), "tab3_L16": (0, 2)}[cfg.name]
-    sc = synth.make_scene(cfg.replace(H=16, W=64, views=1))
-    ds = mixrt.DeviceScene.from_scene(sc, "cuda:0")
-    r = mixrt.Renderer(0)
-    plan = r.launch_plan(ds)
-    r.close()
+_K1 = synth.VIEW720P.replace(name="k1", K=1)
+_K2 = synth.VIEW720P.replace(name="k2", K=2)
+_K3 = synth.VIEW720P.replace(name="k3", K=3)
+_COARSE = synth.VIEW720P.replace(name="coarse_k1", K=1, N_max=1024)
+
+
+@pytest.mark.parametrize("cfg,W,H,want", [
+    (synth.VIEW720P, 0, 0, (13, 2)), (synth.VIEW720P_DENSE, 0, 0, (9, 2)),
+    (synth.VIEW720P_DENSE.replace(name="dense_k4", K=4), 0, 0, (11, 2)),
+    (_K1, 0, 0, (9, 2)), (_K1, 2560, 1440, (10, 2)), (_K1, 4096, 2160, (12, 2)),
+    (_K1, 7680, 4320, (13, 2)), (_K1, 320, 180, (13, 2)), (_COARSE, 1280, 720, (11, 2)),
+    (_COARSE, 2560, 1440, (13, 2)),
+    (_K2, 0, 0, (10, 2)), (_K2, 2560, 1440, (12, 2)), (_K3, 0, 0, (10, 2)),
+    (_K3, 2560, 1440, (12, 2)), (_K3, 4096, 2160, (13, 2)),
+    (synth.VIEW720P.replace(name="fine_spacing", delta=1e-4), 0, 0, (16, 2)),
+    (synth.BATCH8X1080P, 0, 0, (8, 2)), (synth.BATCH8X1080P.replace(name="batch_k4", K=4), 0, 0, (12, 2)),
+    (synth.PAPER720P, 0, 0, (4, 4)), (synth.DEPLOYED720P, 0, 0, (4, 4)),
+    (synth.TABLE3[0], 0, 0, (0, 2)), (_table3("tab3_L8_T5"), 0, 0, (8, 2)),
+    (_table3("tab3_L16_T17").replace(name="tab3_L16"), 0, 0, (0, 2))],
+    ids=lambda c: c.name if hasattr(c, "name") else str(c).replace(" ", ""))
+def test_default_gather_plan_follows_the_rule(cfg, W, H, want):
+    """4-byte entries, among hashed levels finer than the sample spacing: block
+    gathers on the three finest levels; at K < 4 on the 3 to 7 whose cells are
+    at most 4 (K = 1) or 2 far pixels wide; in rounds of one sample per ray on
+    five, seven from K = 8 on; when a level's table exceeds one XCD's L2 on
+    four, and eight at K >= 8.  8-byte (fp16 F = 4) entries: on every hashed
+    level when there are 8 or more of them in tables of 2^10 or more entries.
+    Batches of 4 hashed levels only for entries of 8+ bytes when that covers
+    every hashed level.  W, H: the frame (0: the workload's own)."""
+    plan = _plan(cfg, W or cfg.W, H or cfg.H, 1 if W else cfg.views)
     assert (plan["block_from"], plan["hash_batch"]) == want, plan
+
+
+@pytest.mark.parametrize("cfg,filled,less", [(_K1, 9, 13), (_K3, 9, 13), (synth.VIEW720P_DENSE, 9, 11)],
+                         ids=lambda c: c.name if hasattr(c, "name") else str(c))
+def test_more_block_levels_only_where_the_card_is_full(cfg, filled, less):
+    """The extra levels at K < 4 and in rounds of one take a tile for each of 3
+    waves per SIMD."""
+    waves = 12 * torch.cuda.get_device_properties(0).multi_processor_count
+    R = 64 // cfg.K
+    RH = 2 if R == 16 else 4 if R == 64 else 1
+    for tiles, want in ((waves, filled), (waves - 1, less)):
+        assert _plan(cfg, R // RH * tiles, RH)["block_from"] == want, (tiles, want)
 
 
 @pytest.mark.parametrize("cfg", [synth.VIEW720P, synth.PAPER720P, synth.BATCH8X1080P,
