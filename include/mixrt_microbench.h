@@ -76,11 +76,11 @@ int mixrt_mb_mfma(int iters, int blocks, float *out, void *stream);
  * most K) replays the early-termination path with rounds of chunk samples
  * as it runs when every ray hits and none stops (runs of K/chunk tiles per
  * wave, lane s*chunk + j on sample c*chunk + j of the run's ray s in round
- * c).  block_from: hashed levels from this one on (4-byte entries only) are
+ * c).  block_from: hashed levels from this one on (4- and 8-byte entries) are
  * gathered as the render kernel gathers them there, one aligned 16-byte
  * block per x-neighbour corner pair plus the x + 1 entries of voxels that
- * straddle two blocks, one level per batch (as returned by
- * mixrt_render_launch_shape; L: none); hash_batch: hashed levels per batch
+ * straddle two blocks, one level per batch of 4-byte entries and two of
+ * 8-byte ones (as returned by mixrt_render_launch_shape; L: none); hash_batch: hashed levels per batch
  * of the other gathers, 2 or 4 (4 only for entries of 8 or more bytes, as
  * the render kernel batches them).  N: host int32 [L], the level
  * resolutions (non-decreasing).  work: NULL or device uint32

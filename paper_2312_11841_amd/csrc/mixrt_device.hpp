@@ -65,9 +65,11 @@ struct GridParams {
     float Nf[kMaxLevels];   // N as float, and N - 1 (exact: N <= 2^20), so
     float Ntop[kMaxLevels]; // that no lane converts them
     int32_t block_from;     // levels from here on load x-neighbour corner pairs
-                            // as 16-byte blocks (4-byte entries; L: none)
+                            // as 16-byte blocks (4- and 8-byte fp16 entries;
+                            // L: none)
     int32_t far_last;       // 4-byte entries: a straddling voxel's x + 1 entries
-                            // after all four blocks (else each with its block)
+                            // after all four blocks (else, and for 8-byte
+                            // entries always, each with its block)
     int32_t hash_batch;     // hashed levels per batch of gathers: 2, or 4
                             // (entries of 8 or more bytes)
 };

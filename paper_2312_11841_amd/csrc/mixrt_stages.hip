@@ -71,14 +71,6 @@ __global__ __launch_bounds__(kBlock) void hash_encode_kernel(GridParams gp, cons
     }
 }
 
-// The features alone, which is what a program that keeps them asks for.  A
-// wave takes 64 queries, one or two levels' gathers in flight, and collects up to
-// 32 features of each in LDS; they leave in rows of 16-byte stores past the
-// caches (written once, and the table's lines stay).  Written from the lanes
-// as they come, one 4-byte store per feature touches 64 lines and most lines
-// come back to memory in pieces: 473 us for 1.84 M queries of 16 levels
-// against 148 (236 MB written).  Neighbouring waves go to one XCD, whose L2
-// serves the voxels they share.
 // Block -> logical block: runs of `run` consecutive blocks go to one XCD
 // (hardware block b runs on XCD b mod 8), the XCDs' runs one after another.
 // The grid is a multiple of 8 run.
@@ -103,6 +95,14 @@ __device__ __forceinline__ void features_of(const GridParams &gp, int l, float x
         for (int i = 0; i < F; ++i) col[g * F + i] = f[g][i];
 }
 
+// The features alone, which is what a program that keeps them asks for.  A
+// wave takes 64 queries, one or two levels' gathers in flight, and collects up to
+// 32 features of each in LDS; they leave in rows of 16-byte stores past the
+// caches (written once, and the table's lines stay).  Written from the lanes
+// as they come, one 4-byte store per feature touches 64 lines and most lines
+// come back to memory in pieces: 489 us for the 640x360 view's 1.84 M queries of
+// 16 levels against 164 (236 MB written).  Neighbouring waves go to one XCD, whose L2
+// serves the voxels they share.
 template <int F, bool TF16>
 __global__ __launch_bounds__(kBlock) void hash_features_kernel(GridParams gp,
                                                                const float *__restrict__ x,
@@ -415,17 +415,18 @@ hipError_t launch_hash_encode(const GridParams &gp, int F, bool tf16, const floa
     if (of && !oc && !oi && !ow) {
         GridParams g = gp;
         // the finest hashed levels in 16-byte blocks: 6 of 4-byte entries, 3 of
-        // 8-byte ones (the 640x360 view's 1.84 M queries 177 us with 3, 173 with
-        // 6 and with 9; Tab. 3's 8 levels of 8-byte entries 99.8 with 3, 101.8
-        // with 6)
+        // 8-byte ones (the 640x360 view's 1.84 M queries along rays 167 us with 3,
+        // 164 with 6 and with 9; Tab. 3's 8 levels of 8-byte entries 126 with none,
+        // 130 with 3, 132 with 6, and 4 levels of 2^21 of them at scattered
+        // positions 543, 532)
         const int from = tf16 ? g.L - (F == 2 ? 6 : 3) : g.L;
         g.block_from = from > g.n_dense ? from : g.n_dense;
         const int wide = (g.L * F) % 4 == 0 && ((uintptr_t)of & 15) == 0;
         const int64_t nb = (n + kBlock - 1) / kBlock;
         // Runs of 64 blocks keep neighbouring queries in one L2 (1280x720 queries
-        // of one sample per pixel 167 us without runs, 150 in runs of 16, 143 of
-        // 64), 8 or more of them per XCD keep the XCDs evenly loaded (one eighth
-        // of 1.84 M queries each: 204 us against 168)
+        // of one sample per pixel 157 us without runs, 139 in runs of 16, 130 of
+        // 64), 8 or more of them per XCD keep the XCDs evenly loaded (the 1.84 M
+        // queries in one run per XCD: 227 us)
         const int64_t run = nb / 64 < 1 ? 1 : nb / 64 > 64 ? 64 : nb / 64;
         const dim3 grid((unsigned)((nb + 8 * run - 1) / (8 * run) * (8 * run)));
 #define LAUNCH(FF, TT)                                                                         \

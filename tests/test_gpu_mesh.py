@@ -7,17 +7,8 @@ Bars, for pixels the oracle does not flag as ambiguous (a hit within the
 rounding reach of an edge, another triangle within it in depth, or a near
 miss; grazing rays widen that reach):
   - triangle index and hit/miss: bit-exact;
-  - t: |dt| <= (1e-5 t + 1e-6 D S) / |cos|.  The fp32 ray direction carries
-    about 2e-7 relative error, which moves the hit by t 2e-7 / |cos| along
-    the ray; the fp32 Moller-Trumbore solve forms t from products of
-    vectors of length ~D (D = the farthest vertex's distance from the
-    camera), so it adds a few ulp of D times the condition number S / |cos|
-    (S = L_max^2 / (2 area), about 1 / sin of the smallest corner angle);
-    both coefficients leave a 10x margin or more;
-  - uv: |duv| <= spread (1e-4 + 1e-6 D S / L_max) / |cos| + 1e-6, spread =
-    the largest uv difference between the triangle's corners (the
-    barycentric error of the moved hit point, ~ulp(D) S / L_max, times the
-    uv range it scales); exactly 0 for a mesh without uv;
+  - t and uv: the bars of tests/meshbars.py, which says what they rest on;
+    uv exactly 0 for a mesh without uv;
   - normal: 1e-4 absolute (edges are differenced in fp32 on the GPU).
 Ambiguous pixels: the GPU's triangle must be one the oracle also finds hit or
 nearly hit, at the same distance, no farther than the nearest hit's reach;
