@@ -545,7 +545,7 @@ def main():
             "route": args.geometry + " (in the timed step)",
             "raster_ms": round(ras_ms, 4),
             "raster_kernels": "clear + raster (wave-balanced triangle x pixel pairs, 64-bit "
-                              "atomic min) + resolve",
+                              "atomic min; large boxes listed and drawn in slices) + resolve",
             "raycast_ms": round(ray_ms, 4),
             "raycast_kernel": "uniform-grid walk with empty-space leaps + fp32 Moller-Trumbore",
             "render_ms": round(render_ms, 4),
